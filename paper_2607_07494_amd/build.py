@@ -25,7 +25,7 @@ ARCH = "gfx950"
 CALIB_SOURCE = "calib.hip"
 CALIB_LIB = os.path.join(PKG, "libgift_calib.so")
 
-SOURCES = ["gift_api.cpp", "k_tile.hip", "k_reduce.hip", "k_factor.hip", "k_syrk.hip", "k_update.hip", "k_stream.hip",
+SOURCES = ["gift_api.cpp", "k_tile.hip", "k_reduce.hip", "k_factor.hip", "k_small.hip", "k_syrk.hip", "k_update.hip", "k_stream.hip",
            "k_lowrank.hip", "k_chol.hip", "k_mx.hip"]
 
 

@@ -13,19 +13,21 @@
 // products run once per group on the FP32 MFMA kernels with the group's
 // members as the batch dimension, and the groups advance in lockstep so that
 // each k x k step is ONE launch over every member of every group: one
-// workgroup per member, float64, in LDS when k <= 128.
+// workgroup per member, float64.  Up to k = 256 the Cholesky and, above
+// k = 64, the eigensolver are those of k_small.hip; the rest is here:
 //
-// Cholesky (right-looking, one barrier per column; R^T kept in the strict
-// lower triangle) and the inverse of R by forward substitution on R^T, four
-// lanes per column.  The eigensolver is one-sided (Hestenes) Jacobi with
-// round-robin parallel ordering: rotating the columns of the symmetric
-// positive semidefinite B until they are mutually orthogonal yields
-// B V = V diag(theta), so column norms are the eigenvalues and normalised
-// columns the eigenvectors.  In LDS each column pair is held by 16 lanes in
-// registers between its dot products and its rotation, and the dot products
-// are reduced with DPP row rotations, which leave bit-identical sums on the
-// 16 lanes (every step adds the same two operands on both partner lanes), so
-// all lanes of a pair take the same rotation.
+// Above k = 256 the Cholesky is right-looking, one barrier per column, R^T
+// kept in the strict lower triangle, and the inverse of R goes by forward
+// substitution on R^T.  Up to k = 64 and above k = 256 the eigensolver is
+// one-sided (Hestenes) Jacobi with round-robin parallel ordering: rotating
+// the columns of the symmetric positive semidefinite B until they are
+// mutually orthogonal yields B V = V diag(theta), so column norms are the
+// eigenvalues and normalised columns the eigenvectors.  In LDS each column
+// pair is held by 16 lanes in registers between its dot products and its
+// rotation, and the dot products are reduced with DPP row rotations, which
+// leave bit-identical sums on the 16 lanes (every step adds the same two
+// operands on both partner lanes), so all lanes of a pair take the same
+// rotation.
 //
 // The next refresh warm-starts from the rotated basis Q V (all k columns,
 // descending Ritz values), which leaves B nearly diagonal after one more
@@ -48,6 +50,7 @@
 #include <vector>
 
 #include "gift_internal.h"
+#include "k_small.h"
 
 namespace gift {
 
@@ -57,12 +60,8 @@ gift_status launch_syrk_bf16(gift_ctx *ctx, const uint16_t *const *x_table, int 
 namespace {
 
 constexpr int kSmallThreads = 1024;
-constexpr int kLdsK = 128;   // k handled in LDS by the small kernels
-// Columns count as orthogonal once |<p,q>| <= 1e-10 |p| |q|: B comes from
-// float32 products (relative noise ~1e-7), so rotating further changes nothing
-// the codec can see.
-constexpr double kJacobiTol = 1e-10;
-constexpr int kEigRegs = 16;   // global eigensolver: a column pair in registers up to k = 256
+constexpr int kEigLdsK = 64;     // k of the one-workgroup LDS eigensolver
+constexpr int kLayoutRows = 128; // rows of U that finalize_layout_kernel transposes at a time
 
 // One factor side of the refresh.  The side's persistent state, then its
 // slices of the group buffers.
@@ -77,17 +76,6 @@ struct Member {
   uint32_t seed_lo, seed_hi;
   int mode;              // 0 cold start, 1 warm start, 2 imported U + start rows
   float damping;
-};
-
-// One member's k x k step: partial products in, factor or eigenpairs out.
-struct SmallJob {
-  const float *part;     // [ks][k][k] split-K partials of the k x k product
-  float *out;            // R^-1 (Cholesky) or V (eigensolver), [k][k] row-major
-  float *theta;          // eigenvalues [k] (eigensolver)
-  double *W;             // [k][k+1] float64 scratch when k > kLdsK
-  double *aux;           // [2k + 64] float64 scratch when k > kLdsK
-  int ks, k;
-  float *rout;           // optional R [k][k] (Cholesky, upper triangular)
 };
 
 __device__ __forceinline__ uint32_t philox_word0(uint32_t c0, uint32_t c1, uint32_t c2,
@@ -309,126 +297,6 @@ __device__ __forceinline__ void chol_inv_body(const float *part, int ks, int k, 
     }
 }
 
-// ---------------------------------------------------------------------------
-// The same factorisation for k <= 128 with the matrices in registers.
-// Thread (ty, tx) of a 32 x 32 grid (1024 threads) owns the 4 x 4 block at
-// rows 4 ty.., columns 4 tx.. of G when tx >= ty (upper triangle) and of
-// X = L^-1 when tx <= ty (lower triangle).  Column step j, with d =
-// max(G_jj, floor) and rs = 1 / sqrt(d):
-//   the half-wave of block row j / 4 reads G_jj from the lane of the
-//   diagonal block, scales its rows j of G and X by rs, keeps the scaled X
-//   row (final) and broadcasts both through LDS:
-//     l_b = G_jb rs = R_jb = L_bj (b >= j),   x_b = X_jb rs (b <= j);
-//   after one barrier every thread updates its blocks with FMAs only:
-//     G_ab -= l_a l_b                     (Cholesky trailing update)
-//     X_ab -= l_a x_b   for a > j         (Gauss-Jordan on [L | I])
-// Two broadcast buffers alternate, so one barrier per column suffices.
-// Rows of G at or above j are never read again, so the G update runs over
-// whole blocks (stale broadcast entries only reach those rows); the X update
-// is restricted to rows below j, whose broadcast entries are current.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSmallThreads) void chol_inv_lds_kernel(const SmallJob *jobs) {
-  __shared__ double lb[2][kLdsK], xb[2][kLdsK];   // broadcast rows of R and X
-  __shared__ double dsum[32];
-  const SmallJob J = jobs[blockIdx.x];
-  const int k = J.k, ks = J.ks;
-  const int tid = threadIdx.x, tx = tid & 31, ty = tid >> 5;
-  const int64_t kk = (int64_t)k * k;
-  const bool own_g = tx >= ty, own_x = tx <= ty;
-  double G[4][4], X[4][4];
-  // G = sum of the split-K partials (rows / columns past k stay zero)
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      G[u][w] = 0.0;
-      X[u][w] = (4 * ty + u == 4 * tx + w && 4 * ty + u < k) ? 1.0 : 0.0;
-    }
-  if (own_g) {
-    for (int z = 0; z < ks; ++z) {
-      const float *P = J.part + z * kk;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const int a = 4 * ty + u, b = 4 * tx + w;
-          G[u][w] += (a < k && b < k) ? (double)P[a * k + b] : 0.0;
-        }
-    }
-  }
-  // pivot floor from the trace (every thread sums the 32 block sums in order)
-  if (tx == ty) dsum[ty] = G[0][0] + G[1][1] + G[2][2] + G[3][3];
-  __syncthreads();
-  double tr = 0.0;
-  for (int i = 0; i < 32; ++i) tr += dsum[i];
-  const double floor = 1e-12 * (tr > 0.0 ? tr : 0.0) / (k > 0 ? k : 1) + 1e-300;
-  const int half = (tid & 32);   // lane offset of this thread's half-wave
-
-  for (int j = 0; j < k; ++j) {
-    const int buf = j & 1, jr = j >> 2, ju = j & 3;
-    if (ty == jr) {   // one half-wave: pivot, scaling, broadcast
-      double gd = 0.0;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (u == ju) gd = G[u][u];
-      // G_jj from the diagonal block's lane (tx = jr) of this half-wave
-      const int src = half + jr;
-      const int lo = __builtin_amdgcn_readlane(__double2loint(gd), src);
-      const int hi = __builtin_amdgcn_readlane(__double2hiint(gd), src);
-      const double d0 = __hiloint2double(hi, lo);
-      const double d = d0 > floor ? d0 : floor;
-      const double rs = 1.0 / sqrt(d);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const int col = 4 * tx + w;
-        double gv = 0.0, xv = 0.0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (u == ju) {
-            X[u][w] *= rs;   // row j of X is final from here on
-            gv = G[u][w];
-            xv = X[u][w];
-          }
-        const double lv = own_g && col >= j ? gv * rs : 0.0;   // R_j,col
-        lb[buf][col] = lv;
-        xb[buf][col] = own_x ? xv : 0.0;
-        if (J.rout && col < k) J.rout[(int64_t)j * k + col] = (float)lv;
-      }
-    }
-    __syncthreads();
-    double la[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) la[u] = lb[buf][4 * ty + u];
-    if (own_g && 4 * ty + 3 > j) {
-      double lc[4];
-#pragma unroll
-      for (int w = 0; w < 4; ++w) lc[w] = lb[buf][4 * tx + w];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) G[u][w] -= la[u] * lc[w];
-    }
-    if (own_x && 4 * ty + 3 > j) {
-      double xc[4];
-#pragma unroll
-      for (int w = 0; w < 4; ++w) xc[w] = xb[buf][4 * tx + w];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (4 * ty + u > j)
-#pragma unroll
-          for (int w = 0; w < 4; ++w) X[u][w] -= la[u] * xc[w];
-    }
-  }
-  // R^-1 = X^T (upper triangular), row-major: element (i, c) = X[c][i]
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int c = 4 * ty + u, i = 4 * tx + w;
-      if (c < k && i < k) J.out[i * k + c] = own_x ? (float)X[u][w] : 0.f;
-    }
-}
-
 constexpr int kCholGlobalThreads = 512;   // 64-bit addresses need the register room
 __global__ __launch_bounds__(kCholGlobalThreads) void chol_inv_global_kernel(const SmallJob *jobs) {
   const SmallJob J = jobs[blockIdx.x];
@@ -486,12 +354,13 @@ __device__ __forceinline__ void load_sym(const float *part, int ks, int k, doubl
 __device__ __forceinline__ void rr_emit(const double *W, const double *norms, int *perm, int k, float *V,
                         float *theta) {
   const int tid = threadIdx.x, nt = blockDim.x;
+  // (a NaN norm ranks last: the ranks are a permutation whatever the norms)
   for (int j = tid; j < k; j += nt) {
-    const double v = norms[j];
+    const double v = norms[j], kv = v == v ? v : -1.0;
     int rank = 0;
     for (int l = 0; l < k; ++l) {
-      const double u = norms[l];
-      rank += (u > v) || (u == v && l < j);
+      const double u = norms[l], ku = u == u ? u : -1.0;
+      rank += (ku > kv) || (ku == kv && l < j);
     }
     theta[rank] = (float)v;
     perm[rank] = j;
@@ -506,21 +375,20 @@ __device__ __forceinline__ void rr_emit(const double *W, const double *norms, in
   }
 }
 
-// LDS eigensolver, k <= 128: 64 pairs x 16 lanes (1024 threads).  Lane l16
+// LDS eigensolver, k <= 64: 32 pairs x 16 lanes (512 threads).  Lane l16
 // of pair group g holds rows ((e + g) mod nb) * 16 + l16 of both columns in
 // slot e (nb = ceil(k / 16) blocks of 16 rows), so the four pairs of a wave
 // read four different row blocks at every slot.  Sweeps stop after the first
 // one whose largest rotated |<p,q>| / (|p| |q|) is at most kJacobiLast: the
 // next sweep would leave only about its square (far below the float32 noise
 // of B) and rotate nothing the codec can see.
-constexpr int kEigThreads = 1024;
-constexpr double kJacobiLast = 1e-6;
+constexpr int kEigThreads = 512;
 __global__ __launch_bounds__(kEigThreads) void rr_eig_lds_kernel(const SmallJob *jobs,
                                                                  int max_sweeps) {
-  __shared__ double W[kLdsK * kLdsK];
+  __shared__ double W[kEigLdsK * kEigLdsK];
   __shared__ double zpad[16], sink[16];   // loads of masked slots / their stores
-  __shared__ double norms[kLdsK];
-  __shared__ int perm[kLdsK];
+  __shared__ double norms[kEigLdsK];
+  __shared__ int perm[kEigLdsK];
   __shared__ int any_rot, any_big;
   const SmallJob J = jobs[blockIdx.x];
   const int k = J.k, tid = threadIdx.x;
@@ -530,10 +398,10 @@ __global__ __launch_bounds__(kEigThreads) void rr_eig_lds_kernel(const SmallJob 
   const int kp = (k + 1) & ~1, npairs = kp / 2;
   const int pi = tid >> 4, l16 = tid & 15, gw = (tid >> 4) & 3;
   const int nb = (k + 15) >> 4;
-  int rows[8];
-  bool rv[8];
+  int rows[4];
+  bool rv[4];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
+  for (int e = 0; e < 4; ++e) {
     rows[e] = e < nb ? ((e + gw) % nb) * 16 + l16 : 0;
     rv[e] = e < nb && rows[e] < k;
   }
@@ -552,18 +420,18 @@ __global__ __launch_bounds__(kEigThreads) void rr_eig_lds_kernel(const SmallJob 
         valid = q < k;
       }
       double *cp = W + p * k, *cq = W + q * k;
-      double a[8], b[8];
+      double a[4], b[4];
       double alpha = 0.0, beta = 0.0, gamma = 0.0;
       // unconditional loads: a masked slot reads zeros from zpad (guarded
       // loads would each wait for the one before)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < 4; ++e) {
         const bool ok = valid && rv[e];
         a[e] = *(ok ? cp + rows[e] : zpad + l16);
         b[e] = *(ok ? cq + rows[e] : zpad + l16);
       }
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < 4; ++e) {
         alpha += a[e] * a[e];
         beta += b[e] * b[e];
         gamma += a[e] * b[e];
@@ -576,7 +444,7 @@ __global__ __launch_bounds__(kEigThreads) void rr_eig_lds_kernel(const SmallJob 
         double c, s;
         jacobi_cs(alpha, beta, gamma, c, s);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < 4; ++e) {
           *(rv[e] ? cp + rows[e] : sink + l16) = c * a[e] - s * b[e];
           *(rv[e] ? cq + rows[e] : sink + l16) = s * a[e] + c * b[e];
         }
@@ -594,7 +462,7 @@ __global__ __launch_bounds__(kEigThreads) void rr_eig_lds_kernel(const SmallJob 
   for (int c = pi; c < k; c += kEigThreads / 16) {
     double s = 0.0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int e = 0; e < 4; ++e) {
       const double v = *(rv[e] ? W + c * k + rows[e] : zpad + l16);
       s += v * v;
     }
@@ -605,10 +473,8 @@ __global__ __launch_bounds__(kEigThreads) void rr_eig_lds_kernel(const SmallJob 
   rr_emit(W, norms, perm, k, J.out, J.theta);
 }
 
-// Global-memory eigensolver for k > 128 (same ordering, rotations and stop
-// rule as the LDS one): up to k = 256 each lane loads its elements of a
-// column pair into registers together, then rotates them from there; past
-// that it re-reads the columns.
+// Global-memory eigensolver for k > 256 (same ordering, rotations and stop
+// rule as the LDS one).
 __global__ __launch_bounds__(kSmallThreads) void rr_eig_global_kernel(const SmallJob *jobs,
                                                                       int max_sweeps) {
   __shared__ int any_rot, any_big;
@@ -641,67 +507,28 @@ __global__ __launch_bounds__(kSmallThreads) void rr_eig_global_kernel(const Smal
         }
         double alpha = 0.0, beta = 0.0, gamma = 0.0;
         double *cp = W + (int64_t)p * k, *cq = W + (int64_t)q * k;
-        if (k <= 16 * kEigRegs) {
-          // the lane's elements of both columns loaded together into registers
-          // (one round trip, not one per element), the same sums in the same
-          // order, and the rotation from the registers
-          double va[kEigRegs], vb[kEigRegs];
-#pragma unroll
-          for (int u = 0; u < kEigRegs; ++u) {
-            const int i = l16 + 16 * u;
-            va[u] = valid && i < k ? cp[i] : 0.0;
-            vb[u] = valid && i < k ? cq[i] : 0.0;
+        if (valid) {
+          for (int i = l16; i < k; i += 16) {
+            const double a = cp[i], b = cq[i];
+            alpha += a * a;
+            beta += b * b;
+            gamma += a * b;
           }
-#pragma unroll
-          for (int u = 0; u < kEigRegs; ++u)
-            if (l16 + 16 * u < k) {
-              alpha += va[u] * va[u];
-              beta += vb[u] * vb[u];
-              gamma += va[u] * vb[u];
-            }
-          alpha = row16_sum(alpha);
-          beta = row16_sum(beta);
-          gamma = row16_sum(gamma);
-          if (valid && gamma != 0.0 && fabs(gamma) > kJacobiTol * sqrt(alpha * beta)) {
-            double c, s;
-            jacobi_cs(alpha, beta, gamma, c, s);
-#pragma unroll
-            for (int u = 0; u < kEigRegs; ++u) {
-              const int i = l16 + 16 * u;
-              if (i < k) {
-                cp[i] = c * va[u] - s * vb[u];
-                cq[i] = s * va[u] + c * vb[u];
-              }
-            }
-            if (l16 == 0) {
-              any_rot = 1;
-              if (gamma * gamma > last2 * (alpha * beta)) any_big = 1;
-            }
+        }
+        alpha = row16_sum(alpha);
+        beta = row16_sum(beta);
+        gamma = row16_sum(gamma);
+        if (valid && gamma != 0.0 && fabs(gamma) > kJacobiTol * sqrt(alpha * beta)) {
+          double c, s;
+          jacobi_cs(alpha, beta, gamma, c, s);
+          for (int i = l16; i < k; i += 16) {
+            const double a = cp[i], b = cq[i];
+            cp[i] = c * a - s * b;
+            cq[i] = s * a + c * b;
           }
-        } else {
-          if (valid) {
-            for (int i = l16; i < k; i += 16) {
-              const double a = cp[i], b = cq[i];
-              alpha += a * a;
-              beta += b * b;
-              gamma += a * b;
-            }
-          }
-          alpha = row16_sum(alpha);
-          beta = row16_sum(beta);
-          gamma = row16_sum(gamma);
-          if (valid && gamma != 0.0 && fabs(gamma) > kJacobiTol * sqrt(alpha * beta)) {
-            double c, s;
-            jacobi_cs(alpha, beta, gamma, c, s);
-            for (int i = l16; i < k; i += 16) {
-              const double a = cp[i], b = cq[i];
-              cp[i] = c * a - s * b;
-              cq[i] = s * a + c * b;
-            }
-            if (l16 == 0) {
-              any_rot = 1;
-              if (gamma * gamma > last2 * (alpha * beta)) any_big = 1;
-            }
+          if (l16 == 0) {
+            any_rot = 1;
+            if (gamma * gamma > last2 * (alpha * beta)) any_big = 1;
           }
         }
         __syncthreads();
@@ -772,7 +599,7 @@ __global__ __launch_bounds__(256) void finalize_coef_kernel(const Member *mem) {
 // U diag(c_inv) as [dim, r] through an LDS transpose of 32-row tiles.
 constexpr int kTileRows = 32;
 __global__ __launch_bounds__(256) void finalize_layout_kernel(const Member *mem) {
-  __shared__ float tile[kLdsK][kTileRows + 1];
+  __shared__ float tile[kLayoutRows][kTileRows + 1];
   const Member M = mem[blockIdx.y];
   const int tid = threadIdx.x;
   const int64_t ntiles = (M.dim + kTileRows - 1) / kTileRows;
@@ -788,8 +615,8 @@ __global__ __launch_bounds__(256) void finalize_layout_kernel(const Member *mem)
         if (a < M.r) M.Ut[(int64_t)a * M.dim + i0 + ii] = v;
       }
     }
-    for (int a0 = 0; a0 < M.r; a0 += kLdsK) {
-      const int ac = M.r - a0 < kLdsK ? M.r - a0 : kLdsK;
+    for (int a0 = 0; a0 < M.r; a0 += kLayoutRows) {
+      const int ac = M.r - a0 < kLayoutRows ? M.r - a0 : kLayoutRows;
       __syncthreads();
       for (int t = tid; t < ac * kTileRows; t += 256) {
         const int a = t / kTileRows, ii = t % kTileRows;
@@ -934,17 +761,19 @@ gift_status launch_statistics(gift_ctx *ctx, const void *const *d_xtab, const vo
 
 gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs, int64_t T,
                                  gift_dtype dtype, int32_t iters) {
-  // groups in launch order: LDS-sized k first, so the small-kernel tables
-  // split into one LDS range and one global range
-  std::map<std::tuple<bool, int64_t, int>, Group> by_key;
+  // groups in launch order by the kernels their k x k steps take, so that
+  // each of those covers one range of the small-kernel tables
+  const auto kind = [](int k) { return k <= kEigLdsK ? 0 : (k <= 128 ? 1 : (k <= kSmallMax ? 2 : 3)); };
+  std::map<std::tuple<int, int64_t, int>, Group> by_key;
   for (const SideJob &j : jobs) {
     if (j.side->r <= 0) continue;
-    Group &g = by_key[std::make_tuple(j.side->k > kLdsK, j.side->dim, (int)j.side->r)];
+    Group &g = by_key[std::make_tuple(kind(j.side->k), j.side->dim, (int)j.side->r)];
     g.jobs.push_back(j);
   }
   if (by_key.empty()) return GIFT_OK;
   std::vector<Group> groups;
-  int total = 0, n_lds = 0;
+  int total = 0, upto[4] = {0, 0, 0, 0};   // table entries of kinds 0 .. c
+  bool split_k = false;
   bool any_cold = false;
   int64_t max_kd = 0;
   for (auto &kv : by_key) {
@@ -958,7 +787,8 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
     g.first = total;
     g.bf16_direct = statistics_direct(dtype, g.dim);
     total += g.G;
-    if (g.k <= kLdsK) n_lds += g.G;
+    for (int c = kind(g.k); c < 4; ++c) upto[c] = total;
+    split_k = split_k || g.ks > 1;
     for (const SideJob &j : g.jobs) any_cold = any_cold || !j.side->have_basis || j.side->fill_tail;
     max_kd = std::max<int64_t>(max_kd, (int64_t)g.k * g.dim);
     groups.push_back(std::move(g));
@@ -982,7 +812,8 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
   const size_t o_Q = take(sizeof(float) * qy_floats);
   const size_t o_Y = take(sizeof(float) * qy_floats);
   std::vector<size_t> o_A(groups.size()), o_P(groups.size()), o_R(groups.size()), o_V(groups.size()),
-      o_th(groups.size()), o_W(groups.size()), o_aux(groups.size()), o_X(groups.size());
+      o_th(groups.size()), o_W(groups.size()), o_aux(groups.size()), o_X(groups.size()), o_sum(groups.size()),
+      o_fl(groups.size());
   for (size_t gi = 0; gi < groups.size(); ++gi) {
     const Group &g = groups[gi];
     const size_t G = g.G, k = g.k, dim = g.dim;
@@ -991,8 +822,10 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
     o_R[gi] = take(sizeof(float) * G * k * k);
     o_V[gi] = take(sizeof(float) * G * k * k);
     o_th[gi] = take(sizeof(float) * G * k);
-    o_W[gi] = k > (size_t)kLdsK ? take(sizeof(double) * G * k * (k + 1)) : 0;
-    o_aux[gi] = k > (size_t)kLdsK ? take(sizeof(double) * G * (2 * k + 64)) : 0;
+    o_W[gi] = take(sizeof(double) * G * k * (k + 1));
+    o_aux[gi] = take(sizeof(double) * G * (2 * k + 64));
+    o_sum[gi] = k <= (size_t)kSmallMax && (g.ks > 1 || k > (size_t)kEigLdsK) ? take(sizeof(double) * G * k * k) : 0;
+    o_fl[gi] = take(sizeof(int) * G * kJacobiSweeps);
     o_X[gi] = (dtype == GIFT_BF16 && !g.bf16_direct) ? take(sizeof(float) * (size_t)T * dim) : 0;
   }
   void *base = nullptr;
@@ -1024,8 +857,10 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
     g.Rinv = reinterpret_cast<float *>(b + o_R[gi]);
     g.V = reinterpret_cast<float *>(b + o_V[gi]);
     g.theta = reinterpret_cast<float *>(b + o_th[gi]);
-    g.Wg = o_W[gi] ? reinterpret_cast<double *>(b + o_W[gi]) : nullptr;
-    g.aux = o_aux[gi] ? reinterpret_cast<double *>(b + o_aux[gi]) : nullptr;
+    g.Wg = reinterpret_cast<double *>(b + o_W[gi]);
+    g.aux = reinterpret_cast<double *>(b + o_aux[gi]);
+    double *const sums = o_sum[gi] ? reinterpret_cast<double *>(b + o_sum[gi]) : nullptr;
+    int *const flags = reinterpret_cast<int *>(b + o_fl[gi]);
     g.Xc = o_X[gi] ? reinterpret_cast<float *>(b + o_X[gi]) : nullptr;
     g.xtab = d_xt + g.first;
     for (int m = 0; m < g.G; ++m) {
@@ -1055,14 +890,18 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
       C.part = g.part + (int64_t)m * g.ks * k2;
       C.out = g.Rinv + (int64_t)m * k2;
       C.theta = nullptr;
-      C.W = g.Wg ? g.Wg + (int64_t)m * g.k * (g.k + 1) : nullptr;
-      C.aux = g.aux ? g.aux + (int64_t)m * (2 * g.k + 64) : nullptr;
+      C.W = g.Wg + (int64_t)m * g.k * (g.k + 1);
+      C.aux = g.aux + (int64_t)m * (2 * g.k + 64);
       C.ks = g.ks;
       C.k = g.k;
+      // (a Cholesky of one partial reads it as it is)
+      C.sum = sums && g.ks > 1 ? sums + m * k2 : nullptr;
+      C.flags = flags + (int64_t)m * kJacobiSweeps;
       SmallJob &E = h_eig[g.first + m];
       E = C;
       E.out = g.V + (int64_t)m * k2;
       E.theta = g.theta + (int64_t)m * g.k;
+      E.sum = sums && g.k > kEigLdsK ? sums + m * k2 : nullptr;
       h_xt[g.first + m] = g.jobs[m].x;
     }
   }
@@ -1149,22 +988,36 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
     j.kernel_family = GIFT_KERNEL_FACTOR;
     return launch_tile(ctx, j);
   };
+  // the k x k step of every member
   auto small_launch = [&](bool eig) -> gift_status {
-    ProfileScope prof(ctx, eig ? GIFT_KERNEL_EIG : GIFT_KERNEL_CHOL);
     const SmallJob *tab = eig ? d_eig : d_chol;
-    if (n_lds > 0) {
-      if (eig)
-        hipLaunchKernelGGL(rr_eig_lds_kernel, dim3(n_lds), dim3(kEigThreads), 0, stream, tab, 40);
-      else
-        hipLaunchKernelGGL(chol_inv_lds_kernel, dim3(n_lds), dim3(kSmallThreads), 0, stream, tab);
+    gift_status e;
+    // (the one-workgroup eigensolvers and a Cholesky without partials sum for themselves)
+    const int first = eig ? upto[0] : 0;
+    if (upto[2] > first && (eig || split_k) &&
+        (e = launch_k_sum(ctx, tab + first, upto[2] - first, upto[2] > upto[1] ? kSmallMax : 128,
+                          GIFT_KERNEL_FACTOR)) != GIFT_OK)
+      return e;
+    if (eig) {
+      if (upto[0] > 0) {
+        ProfileScope prof(ctx, GIFT_KERNEL_EIG);
+        hipLaunchKernelGGL(rr_eig_lds_kernel, dim3(upto[0]), dim3(kEigThreads), 0, stream, tab, 40);
+      }
+      if ((e = launch_eig_blocks(ctx, tab + upto[0], upto[1] - upto[0], 128)) != GIFT_OK ||
+          (e = launch_eig_blocks(ctx, tab + upto[1], upto[2] - upto[1], kSmallMax)) != GIFT_OK)
+        return e;
+    } else if ((e = launch_chol_tiles(ctx, tab, upto[1], 128, false)) != GIFT_OK ||
+               (e = launch_chol_tiles(ctx, tab + upto[1], upto[2] - upto[1], kSmallMax, false)) != GIFT_OK) {
+      return e;
     }
-    if (total > n_lds) {
+    if (total > upto[2]) {
+      ProfileScope prof(ctx, eig ? GIFT_KERNEL_EIG : GIFT_KERNEL_CHOL);
       if (eig)
-        hipLaunchKernelGGL(rr_eig_global_kernel, dim3(total - n_lds), dim3(kSmallThreads), 0, stream,
-                           tab + n_lds, 40);
+        hipLaunchKernelGGL(rr_eig_global_kernel, dim3(total - upto[2]), dim3(kSmallThreads), 0, stream,
+                           tab + upto[2], 40);
       else
-        hipLaunchKernelGGL(chol_inv_global_kernel, dim3(total - n_lds), dim3(kCholGlobalThreads), 0, stream,
-                           tab + n_lds);
+        hipLaunchKernelGGL(chol_inv_global_kernel, dim3(total - upto[2]), dim3(kCholGlobalThreads), 0, stream,
+                           tab + upto[2]);
     }
     return check_launch(eig ? "rr_eig_kernel" : "chol_inv_kernel");
   };
@@ -1222,10 +1075,7 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
 
 size_t chol_blocks_scratch(int k, int count) {
   auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  size_t b = 256;
-  if (k > kLdsK)
-    b += a256(sizeof(double) * (size_t)count * k * (k + 1)) + a256(sizeof(double) * (size_t)count * (2 * k + 64));
-  return b;
+  return a256(sizeof(double) * (size_t)count * k * (k + 1)) + a256(sizeof(double) * (size_t)count * (2 * k + 64));
 }
 
 gift_status launch_chol_blocks(gift_ctx *ctx, const float *G, int k, int count, float *R, float *Rinv,
@@ -1233,22 +1083,18 @@ gift_status launch_chol_blocks(gift_ctx *ctx, const float *G, int k, int count, 
   if (count <= 0 || k <= 0) return GIFT_OK;
   auto a256 = [](size_t x) { return (x + 255) & ~(size_t)255; };
   char *p = static_cast<char *>(scratch);
-  double *W = nullptr, *aux = nullptr;
-  if (k > kLdsK) {
-    W = reinterpret_cast<double *>(p);
-    p += a256(sizeof(double) * (size_t)count * k * (k + 1));
-    aux = reinterpret_cast<double *>(p);
-  }
+  double *const W = reinterpret_cast<double *>(p);
+  double *const aux = reinterpret_cast<double *>(p + a256(sizeof(double) * (size_t)count * k * (k + 1)));
   const int64_t kk = (int64_t)k * k;
   std::vector<SmallJob> h(count);
   for (int z = 0; z < count; ++z) {
     SmallJob &J = h[z];
+    J = SmallJob{};
     J.part = G + z * kk;
     J.out = Rinv + z * kk;
     J.rout = R + z * kk;
-    J.theta = nullptr;
-    J.W = W ? W + (int64_t)z * k * (k + 1) : nullptr;
-    J.aux = aux ? aux + (int64_t)z * (2 * k + 64) : nullptr;
+    J.W = W + (int64_t)z * k * (k + 1);
+    J.aux = aux + (int64_t)z * (2 * k + 64);
     J.ks = 1;
     J.k = k;
   }
@@ -1257,11 +1103,9 @@ gift_status launch_chol_blocks(gift_ctx *ctx, const float *G, int k, int count, 
   gift_status st = upload_table(ctx, TAB_CHOL_BLOCKS, R, h.data(), sizeof(SmallJob) * (size_t)count, &tab);
   if (st != GIFT_OK) return st;
   const SmallJob *d_tab = static_cast<const SmallJob *>(tab);
+  if (k <= kSmallMax) return launch_chol_tiles(ctx, d_tab, count, k, false);
   ProfileScope prof(ctx, GIFT_KERNEL_CHOL);
-  if (k <= kLdsK)
-    hipLaunchKernelGGL(chol_inv_lds_kernel, dim3(count), dim3(kSmallThreads), 0, ctx->stream, d_tab);
-  else
-    hipLaunchKernelGGL(chol_inv_global_kernel, dim3(count), dim3(kCholGlobalThreads), 0, ctx->stream, d_tab);
+  hipLaunchKernelGGL(chol_inv_global_kernel, dim3(count), dim3(kCholGlobalThreads), 0, ctx->stream, d_tab);
   return check_launch("chol_blocks");
 }
 

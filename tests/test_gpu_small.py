@@ -1,0 +1,88 @@
+"""The k x k steps of the factor refresh (runs on an MI355X): the register-tile
+Cholesky and inverse up to 256 and the block Jacobi eigensolver for
+64 < k <= 256, at the edges of their 16-wide tiles, 32-wide column blocks and
+kernel ranges.
+
+Both are float64 inside.  The Cholesky factors are compared with numpy's of the
+same float32 statistics (exported through a Cholesky-form factor): R is stored
+in float32, so a relative error of 2^-23 per entry plus the statistics' own
+rounding over the input's condition number (about 1e3), 1e-3 as the other
+Cholesky tests take.  The eigensolver is compared through S^-1's action with
+the float64 mirror of the refresh (1e-3, the refresh tests' bound).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import codec, subspace
+from synth import factor_inputs, haar
+from test_gpu_factor import action_gap, ctx, exported, say, t  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+gift = pytest.importorskip("paper_2607_07494_amd.gift")
+
+
+@pytest.mark.parametrize("dim,block", [(1, 0), (15, 0), (16, 0), (17, 0), (33, 0), (127, 0), (128, 0), (129, 0),
+                                       (144, 0), (241, 0), (256, 0), (257, 0), (300, 150), (70, 17)])
+def test_cholesky_tiles(ctx, dim, block):  # noqa: F811
+    say(f"chol tiles dim={dim} block={block}")
+    x = factor_inputs(400 + dim, 4 * dim, dim)[0]
+    ref = codec.chol_factor(codec.factor_statistics(x), block, 1e-4)
+    f = gift.CholFactor(ctx, 4, dim, block, gift.SIDE_INPUT, 1e-4)
+    f.update(acts=t(x))
+    R, Ri = (v.cpu().numpy().astype(np.float64) for v in f.export(gift.SIDE_INPUT))
+    for got, want in ((R, ref.R), (Ri, ref.Rinv)):
+        assert np.linalg.norm(got - want) <= 1e-3 * np.linalg.norm(want)
+        assert np.all(np.tril(got, -1) == 0)
+    f.close()
+
+
+@pytest.mark.parametrize("dim,r", [(100, 33), (128, 64), (129, 64), (320, 65), (150, 100), (320, 97), (250, 125),
+                                   (512, 128), (400, 129)])
+def test_eigensolver_blocks(ctx, dim, r):  # noqa: F811
+    """Cold, then warm on other tokens (k = min(dim, 2 r) from 66 to 258)."""
+    say(f"block eigensolver dim={dim} r={r}")
+    X, _ = factor_inputs(500 + dim, 4 * dim, dim)
+    X2, _ = factor_inputs(500 + dim, 3 * dim, dim)
+    f = gift.Factor(ctx, 16, dim, r, gift.SIDE_INPUT, seed=dim)
+    f.update(acts=t(X), iters=3)
+    A = codec.factor_statistics(X)
+    mirror, _ = subspace.subspace_factor(A, r, 3, seed=dim)
+    got = exported(f, gift.SIDE_INPUT)
+    assert action_gap(got, mirror, dim) <= 1e-3
+    np.testing.assert_allclose(got.U.T @ got.U, np.eye(r), atol=1e-5)
+    f.update(acts=t(X2), iters=2)
+    got = exported(f, gift.SIDE_INPUT)
+    np.testing.assert_allclose(got.U.T @ got.U, np.eye(r), atol=1e-5)
+    A2 = codec.factor_statistics(X2)
+    w = np.sort(np.linalg.eigvalsh(A2))[::-1]
+    assert np.trace(got.U.T @ A2 @ got.U) / w[:r].sum() >= 0.999
+    f.close()
+
+
+def test_eigensolver_degenerate_spectra(ctx):  # noqa: F811
+    """A spectrum of two values (every gap zero or large), fewer tokens than the
+    dimension, and no statistics at all."""
+    dim, r = 160, 33
+    rng = np.random.default_rng(3)
+    spec = np.where(np.arange(dim) < r, 4.0, 1.0)
+    X = ((haar(rng, 4 * dim, dim) * np.sqrt(4 * dim)) * np.sqrt(spec) @ haar(rng, dim, dim).T).astype(np.float32)
+    f = gift.Factor(ctx, 16, dim, r, gift.SIDE_INPUT, seed=5)
+    f.update(acts=t(X), iters=12)
+    got, exact = exported(f, gift.SIDE_INPUT), codec.lowrank_factor(codec.factor_statistics(X), r)
+    assert action_gap(got, exact, dim) <= 1e-3
+    assert got.sigma2 == pytest.approx(1.0, rel=1e-4)
+    f.close()
+    Y = rng.standard_normal((80, dim)).astype(np.float32)
+    f = gift.Factor(ctx, 16, dim, r, gift.SIDE_INPUT, damping=1e-3, seed=6)
+    f.update(acts=t(Y), iters=2)
+    got = exported(f, gift.SIDE_INPUT)
+    mirror, _ = subspace.subspace_factor(codec.factor_statistics(Y), r, 2, seed=6, damping=1e-3)
+    assert action_gap(got, mirror, dim) <= 1e-3
+    # all-zero statistics: the identity
+    f.update(acts=torch.zeros((80, dim), device="cuda"), iters=1)
+    got = exported(f, gift.SIDE_INPUT)
+    assert np.all(got.c_fwd == 0) and np.all(got.c_inv == 0) and got.sigma2 == 0.0
+    f.close()
