@@ -26,7 +26,7 @@ CALIB_SOURCE = "calib.hip"
 CALIB_LIB = os.path.join(PKG, "libgift_calib.so")
 
 SOURCES = ["gift_api.cpp", "k_tile.hip", "k_reduce.hip", "k_factor.hip", "k_small.hip", "k_syrk.hip", "k_update.hip", "k_stream.hip",
-           "k_lowrank.hip", "k_chol.hip", "k_mx.hip"]
+           "k_lowrank.hip", "k_strip.hip", "k_chol.hip", "k_mx.hip"]
 
 
 def hipcc() -> str:
@@ -52,7 +52,7 @@ def compile_flags():
 
 # Sources whose compiler resource report is kept (kernel-resource-usage
 # remarks), for the spill check below.
-RESOURCE_REPORT = {"k_lowrank.hip"}
+RESOURCE_REPORT = {"k_lowrank.hip", "k_strip.hip"}
 
 
 def _compile(src: str) -> str:

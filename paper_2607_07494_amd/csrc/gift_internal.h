@@ -278,6 +278,9 @@ bool lr_update_eligible(const TileJob &job);
 // its quantize pass can take the AMAX pass's raw sub-slots (job.from_raw)
 bool lr_quant_reads_raw(const TileJob &job);
 gift_status launch_lr_update(gift_ctx *ctx, const TileJob &job);
+// k_strip.hip: its two passes over column strips (large launches, input side)
+bool lr_strip_eligible(const TileJob &job);
+gift_status launch_lr_strip(gift_ctx *ctx, const TileJob &job);
 bool lr_proj_eligible(const TileJob &job);
 gift_status launch_lr_proj(gift_ctx *ctx, const TileJob &job);
 int lr_proj_parts(int64_t M, int64_t K, int32_t batch);
