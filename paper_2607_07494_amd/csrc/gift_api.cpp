@@ -308,7 +308,19 @@ gift_status plan_low_rank(gift_ctx *ctx, const gift_factor *f, const float *W, i
   // (both sides: the decode's projection alone, summed before its two uses)
   const bool pp_ok = useA && (!useG || inverse) && aligned && n % 4 == 0 &&
                      (A.r == 16 || A.r == 32 || A.r == 64 || A.r == 128);
-  const int pparts = !pp_ok ? 1 : (inverse ? proj_parts(m, n, A.r, N) : lr_proj_parts(m, n, N));
+  // any other shape (odd sizes and alignments, ranks 48, 96, ...): float32
+  // products whose grid of 64-row tiles may be small.  The decode takes its
+  // contraction in partials summed once (1001 x 2731 at rank 48: 132 -> 14 us);
+  // the encode keeps one chain per output (proj_chain_kernel).  (A projection
+  // that fills the chip with 16-row strips takes those instead: aligned, rank
+  // a multiple of 4 but not of 16; so does the two-sided encode's split-bf16
+  // one.)
+  const bool strips = aligned && n % 4 == 0 && A.r % 4 == 0 &&
+                      (!(A.r % 16 == 0 && A.r <= 128) ||
+                       (!inverse && (A.r == 16 || A.r == 32 || A.r == 64 || A.r == 128)));
+  const bool chain = useA && !pp_ok && !strips && !inverse;
+  const int gparts = !useA || pp_ok || strips || !inverse || (m * A.r) % 4 != 0 ? 1 : small_split(m, A.r, N, n);
+  const int pparts = pp_ok ? (inverse ? proj_parts(m, n, A.r, N) : lr_proj_parts(m, n, N)) : gparts;
   // (the in-order sum reads 16-byte groups: a partial's size a multiple of 4)
   // The encode's U_G^T W at rank 64 or 128 takes the split-bf16 transposed
   // projection with its own partial count.
@@ -329,8 +341,9 @@ gift_status plan_low_rank(gift_ctx *ctx, const gift_factor *f, const float *W, i
   }
   // the encode sums the projection's partials once (the update then reads
   // one P per column range instead of all partials), and so does the
-  // two-sided decode (K and L2 read P)
-  const bool presum = (!inverse || useG) && pparts > 1;
+  // two-sided decode (K and L2 read P); only the register-direct update of
+  // the input-side decode sums them itself
+  const bool presum = (!inverse || useG || !pp_ok) && pparts > 1;
   if (presum) {
     Psum = reinterpret_cast<float *>(ws + off);
     off += a256(sizeof(float) * N * m * A.r);
@@ -387,7 +400,7 @@ gift_status plan_low_rank(gift_ctx *ctx, const gift_factor *f, const float *W, i
     j.ksplit = pparts;
     j.split3 = !inverse;
     j.kernel_family = inverse ? GIFT_KERNEL_DECODE_PROJECT : GIFT_KERNEL_PROJECT;
-    if ((st = launch_tile(ctx, j)) != GIFT_OK) return st;
+    if ((st = chain && proj_chain_eligible(j) ? launch_proj_chain(ctx, j) : launch_tile(ctx, j)) != GIFT_OK) return st;
     if (presum &&
         (st = launch_lr_psum(ctx, P, Psum, pparts, m * A.r, N,
                             inverse ? GIFT_KERNEL_DECODE_PROJECT : GIFT_KERNEL_PROJECT)) != GIFT_OK)
@@ -491,7 +504,7 @@ gift_status plan_low_rank(gift_ctx *ctx, const gift_factor *f, const float *W, i
       }
     } else if (presum) {  // P (C_A U_A^T), P already summed
       s.a = Operand{Psum, A.r, m * A.r, true, 1};
-      s.b = Operand{A.Uc, A.r, 0, true};
+      s.b = Operand{inverse ? A.Uci : A.Uc, A.r, 0, true};
       u.col_img = img;
     } else {  // P (C_A U_A^T), P summed from its partials
       s.a = Operand{P, A.r, m * A.r, true, pparts};

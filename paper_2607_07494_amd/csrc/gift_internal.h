@@ -318,6 +318,9 @@ gift_status launch_stream_codec(gift_ctx *ctx, const TileJob &job);
 gift_status launch_stream_reduce(gift_ctx *ctx, const uint8_t *codes, const float *scales, int32_t N,
                                  int64_t m, int64_t n, BlockGeom g, float *mean);
 gift_status launch_proj(gift_ctx *ctx, const TileJob &job);
+// one unsplit chain per output, for grids that leave most of the chip idle
+bool proj_chain_eligible(const TileJob &job);
+gift_status launch_proj_chain(gift_ctx *ctx, const TileJob &job);
 // split-K factor the projection kernel uses for an [batch, M, K] x [C, K]^T
 // product whose consumer can sum partials (1 = a single result)
 int proj_parts(int64_t M, int64_t K, int C, int32_t batch);

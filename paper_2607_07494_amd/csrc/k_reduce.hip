@@ -6,10 +6,11 @@
 // for j = 0..N-1 in order.  The translation unit is compiled without FMA
 // contraction, so the result is bit-for-bit the sequence above.
 //
-// Layout: one workgroup (256 lanes) covers 16 rows x 256 columns; lane t
-// takes row t/16 and the 4-column chunks 4*(t%16) + 64*v, v = 0..3, so each
-// wave-wide access is contiguous (256 B of codes, 1 KiB of output per row).
-// Block scales of the tile are staged in LDS.
+// Layout: one workgroup (256 lanes) covers 16 rows x 64 columns, lane t row
+// t/16 and the four columns 4*(t%16)..: the ranks' loads of a lane are the only
+// ones it has in flight, so narrow workgroups, many of them (1001 x 2731, six
+// ranks: 28 us at 256 columns and one rank's load at a time).  Block scales of
+// the tile are staged in LDS.
 
 #include "fp8_e4m3.h"
 #include "gift_internal.h"
@@ -17,7 +18,7 @@
 namespace gift {
 namespace {
 
-constexpr int kRows = 16, kCols = 256, kThreads = 256;
+constexpr int kRows = 16, kCols = 64, kThreads = 256;
 constexpr int kMaxScales = 4096;
 
 struct RArgs {
@@ -28,8 +29,12 @@ struct RArgs {
   int64_t br, bc;
   int nbr, nbc;
   int N;
-  int vec;
 };
+
+// accesses at any byte's / float's address: rows of an odd length start
+// anywhere, and the memory path takes a wide access there as one
+typedef uint32_t u32u __attribute__((aligned(1)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 __global__ __launch_bounds__(kThreads) void reduce_kernel(const RArgs p) {
   __shared__ float lds_s[kMaxScales];
@@ -37,14 +42,16 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(const RArgs p) {
   const int64_t i0 = (int64_t)blockIdx.y * kRows, j0 = (int64_t)blockIdx.x * kCols;
   const int64_t i1 = i0 + kRows < p.m ? i0 + kRows : p.m;
   const int64_t j1 = j0 + kCols < p.n ? j0 + kCols : p.n;
-  const int64_t bi0 = i0 / p.br, bj0 = j0 / p.bc;
-  const int nlbj = (int)((j1 - 1) / p.bc - bj0 + 1);
-  const int nlb = (int)((i1 - 1) / p.br - bi0 + 1) * nlbj;
+  // (rows and columns fit 31 bits: 32-bit divisions)
+  const uint32_t br = (uint32_t)p.br, bc = (uint32_t)p.bc;
+  const int bi0 = (int)((uint32_t)i0 / br), bj0 = (int)((uint32_t)j0 / bc);
+  const int nlbj = (int)((uint32_t)(j1 - 1) / bc) - bj0 + 1;
+  const int64_t nlb = (int64_t)((int)((uint32_t)(i1 - 1) / br) - bi0 + 1) * nlbj;
   const int64_t nblk = (int64_t)p.nbr * p.nbc;
-  const bool staged = (int64_t)nlb * p.N <= kMaxScales;
+  const bool staged = nlb * p.N <= kMaxScales;
   if (staged) {
-    for (int t = tid; t < nlb * p.N; t += kThreads) {
-      const int j = t / nlb, l = t % nlb;
+    for (int t = tid; t < (int)nlb * p.N; t += kThreads) {
+      const int j = t / (int)nlb, l = t % (int)nlb;
       const int64_t bi = bi0 + l / nlbj, bj = bj0 + l % nlbj;
       lds_s[t] = p.scales[j * nblk + bi * p.nbc + bj];
     }
@@ -54,45 +61,62 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(const RArgs p) {
   const int64_t gi = i0 + tid / 16;
   if (gi >= p.m) return;
   const int q = tid % 16;
-  const int64_t lbi = gi / p.br - bi0;
+  const int lbi = (int)((uint32_t)gi / br) - bi0;
   const int64_t mn = p.m * p.n;
   const float fN = (float)p.N;
+  const int64_t gj = j0 + 4 * q;
+  if (gj >= p.n) return;
+  {
+    const bool full = gj + 3 < p.n;
+    int lbl[4];   // local block of each column
+    {
+      int lbj = (int)((uint32_t)gj / bc);
+      int64_t edge = (int64_t)(lbj + 1) * bc;
+      lbj -= bj0;
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int64_t gj = j0 + 4 * q + 64 * v;
-    if (gj >= p.n) break;
-    const bool full = p.vec && gj + 3 < p.n;
-    int lbl[4];
-    int64_t gbl[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int64_t c = gj + e < p.n ? gj + e : p.n - 1;
-      lbl[e] = (int)(lbi * nlbj + (c / p.bc - bj0));
-      gbl[e] = (gi / p.br) * p.nbc + c / p.bc;
+      for (int e = 0; e < 4; ++e) {
+        if (gj + e == edge && gj + e < p.n) {
+          ++lbj;
+          edge += bc;
+        }
+        lbl[e] = lbi * nlbj + lbj;
+      }
     }
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     const int64_t off = gi * p.n + gj;
-    for (int j = 0; j < p.N; ++j) {
-      uint32_t word;
-      if (full) {
-        word = *reinterpret_cast<const uint32_t *>(p.codes + j * mn + off);
-      } else {
-        word = 0u;
+    auto load = [&](int j) {
+      const uint8_t *c = p.codes + j * mn + off;
+      if (full) return (uint32_t)*reinterpret_cast<const u32u *>(c);
+      uint32_t word = 0u;
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (gj + e < p.n) word |= (uint32_t)p.codes[j * mn + off + e] << (8 * e);
-      }
+      for (int e = 0; e < 4; ++e)
+        if (gj + e < p.n) word |= (uint32_t)c[e] << (8 * e);
+      return word;
+    };
+    // four ranks' codes in flight together (rank order kept in the sums)
+    for (int j0r = 0; j0r < p.N; j0r += 4) {
+      uint32_t word[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float s = staged ? lds_s[j * nlb + lbl[e]] : p.scales[j * nblk + gbl[e]];
-        const float val = e4m3_decode((word >> (8 * e)) & 0xffu) * s;
-        acc[e] = acc[e] + val;
+      for (int u = 0; u < 4; ++u) word[u] = load(j0r + u < p.N ? j0r + u : p.N - 1);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (j0r + u >= p.N) break;
+        float d[4];
+        e4m3_decode4(word[u], d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float s =
+              staged ? lds_s[(j0r + u) * (int)nlb + lbl[e]]
+                     : p.scales[(j0r + u) * nblk + (int64_t)(bi0 + lbl[e] / nlbj) * p.nbc + bj0 + lbl[e] % nlbj];
+          const float val = d[e] * s;
+          acc[e] = acc[e] + val;
+        }
       }
     }
     float *out = p.mean + off;
     if (full) {
-      *reinterpret_cast<float4 *>(out) =
-          make_float4(acc[0] / fN, acc[1] / fN, acc[2] / fN, acc[3] / fN);
+      const float4u o = {acc[0] / fN, acc[1] / fN, acc[2] / fN, acc[3] / fN};
+      *reinterpret_cast<float4u *>(out) = o;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -119,8 +143,6 @@ gift_status launch_reduce(gift_ctx *ctx, const uint8_t *codes, const float *scal
   a.nbr = g.nbr;
   a.nbc = g.nbc;
   a.N = N;
-  a.vec = (n % 4 == 0) && ((reinterpret_cast<uintptr_t>(codes) & 3) == 0) &&
-          ((reinterpret_cast<uintptr_t>(mean) & 15) == 0);
   ProfileScope prof(ctx, GIFT_KERNEL_REDUCE);
   dim3 grid((unsigned)((n + kCols - 1) / kCols), (unsigned)((m + kRows - 1) / kRows));
   hipLaunchKernelGGL(reduce_kernel, grid, dim3(kThreads), 0, ctx->stream, a);

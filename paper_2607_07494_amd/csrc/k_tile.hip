@@ -35,7 +35,6 @@ constexpr int kMaxLocalBlocks = 256;
 struct OperandP {
   const float *ptr;
   int64_t ld, bs;
-  int vec;  // 16-byte loads allowed
   const float *const *tab;   // batch entry b at tab[b] (grouped decode), else ptr + b bs
 };
 struct SegmentP {
@@ -65,8 +64,21 @@ struct KArgs {
   int64_t br, bc;
   int nbr, nbc;
   int shared;
-  int vec_out;  // 16-byte epilogue access allowed
 };
+
+// 16-byte accesses at any float's address and a 4-byte store at any byte's:
+// rows of an odd length start anywhere, and the memory path takes a wide
+// access at such an address as one (four 4-byte ones cost four)
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32u __attribute__((aligned(1)));
+__device__ __forceinline__ float4 ld4u(const float *p) {
+  const float4u v = *reinterpret_cast<const float4u *>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void st4u(float *p, float x, float y, float z, float w) {
+  const float4u v = {x, y, z, w};
+  *reinterpret_cast<float4u *>(p) = v;
+}
 
 template <int ROWS, bool KMAJOR, int kBK>
 struct TileLoader {
@@ -88,8 +100,8 @@ struct TileLoader {
           const int64_t gi = row0 + row, gk = k0 + 4 * kq;
           if (gi < rows) {
             const float *p = base + gi * op.ld + gk;
-            if (op.vec && gk + 3 < K) {
-              v = *reinterpret_cast<const float4 *>(p);
+            if (gk + 3 < K) {
+              v = ld4u(p);
             } else {
               v.x = gk + 0 < K ? p[0] : 0.f;
               v.y = gk + 1 < K ? p[1] : 0.f;
@@ -102,8 +114,8 @@ struct TileLoader {
           const int64_t gk = k0 + kk, gi = row0 + 4 * iq;
           if (gk < K) {
             const float *p = base + gk * op.ld + gi;
-            if (op.vec && gi + 3 < rows) {
-              v = *reinterpret_cast<const float4 *>(p);
+            if (gi + 3 < rows) {
+              v = ld4u(p);
             } else {
               v.x = gi + 0 < rows ? p[0] : 0.f;
               v.y = gi + 1 < rows ? p[1] : 0.f;
@@ -150,14 +162,15 @@ __device__ __forceinline__ float block_max_abs(float a, float b) { return a > b 
 
 // Local scale-block table of one output tile.
 struct LocalBlocks {
-  int64_t bi0, bj0;
+  int bi0, bj0;
   int nlbi, nlbj, nlb;
   __device__ __forceinline__ void init(const KArgs &p, int64_t i0, int64_t j0, int64_t i1,
                                        int64_t j1) {
-    bi0 = i0 / p.br;
-    bj0 = j0 / p.bc;
-    nlbi = (int)((i1 - 1) / p.br - bi0 + 1);
-    nlbj = (int)((j1 - 1) / p.bc - bj0 + 1);
+    // (rows and columns fit 31 bits; a 64-bit division is some 50 instructions)
+    bi0 = (int)((uint32_t)i0 / (uint32_t)p.br);
+    bj0 = (int)((uint32_t)j0 / (uint32_t)p.bc);
+    nlbi = (int)((uint32_t)(i1 - 1) / (uint32_t)p.br) - bi0 + 1;
+    nlbj = (int)((uint32_t)(j1 - 1) / (uint32_t)p.bc) - bj0 + 1;
     nlb = nlbi * nlbj;
   }
 };
@@ -189,7 +202,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
     lb.init(p, i0, j0, i1, j1);
     const int64_t nblk = (int64_t)p.nbr * p.nbc;
     for (int l = tid; l < lb.nlb; l += kThreads) {
-      const int64_t bi = lb.bi0 + l / lb.nlbj, bj = lb.bj0 + l % lb.nlbj;
+      const int64_t bi = lb.bi0 + (uint32_t)l / (uint32_t)lb.nlbj, bj = lb.bj0 + (uint32_t)l % (uint32_t)lb.nlbj;
       if (EPI == EPI_AMAX) {
         if (l < kMaxLocalBlocks) lds_amax[l] = 0u;
       } else {
@@ -221,9 +234,9 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
         float4 d = make_float4(0.f, 0.f, 0.f, 0.f), rr = d;
         if (row_l < BM && gi < p.M && gj < p.N) {
           const int64_t off = (int64_t)b * MN + gi * p.N + gj;
-          if (p.vec_out && gj + 3 < p.N) {
-            d = *reinterpret_cast<const float4 *>(p.D + off);
-            if (p.ef) rr = *reinterpret_cast<const float4 *>(p.ef + off);
+          if (gj + 3 < p.N) {
+            d = ld4u(p.D + off);
+            if (p.ef) rr = ld4u(p.ef + off);
           } else {
             d.x = p.D[off];
             d.y = gj + 1 < p.N ? p.D[off + 1] : 0.f;
@@ -342,13 +355,13 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
     const int64_t gi = i0 + row_l;
     if (row_l >= BM || gi >= p.M) break;
     const int q = tid % TPR;
-    const int64_t lbi = (EPI != EPI_STORE) ? (gi / p.br - lb.bi0) : 0;
+    const int lbi = (EPI != EPI_STORE) ? (int)((uint32_t)gi / (uint32_t)p.br) - lb.bi0 : 0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int col_l = 4 * q + (BN / 4) * v;
       const int64_t gj = j0 + col_l;
       if (gj >= p.N) continue;
-      const bool full = p.vec_out && gj + 3 < p.N;
+      const bool full = gj + 3 < p.N;
       float acc4[4] = {0.f, 0.f, 0.f, 0.f};
       if (GEMM) {
         const float4 c = *reinterpret_cast<const float4 *>(Cs + row_l * (BN + 4) + col_l);
@@ -368,8 +381,8 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
             o[e] = val;
           }
         }
-        if (full && (p.ldc % 4 == 0)) {
-          *reinterpret_cast<float4 *>(cp) = make_float4(o[0], o[1], o[2], o[3]);
+        if (full) {
+          st4u(cp, o[0], o[1], o[2], o[3]);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -377,6 +390,10 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
         }
         continue;
       }
+      // block column of the chunk's first element and columns left in it
+      int lbj = (int)((uint32_t)gj / (uint32_t)p.bc);
+      int left = (int)((int64_t)(lbj + 1) * p.bc - gj);
+      lbj -= lb.bj0;
       // codec: W~ = D + acc (+ R), D and all codec tensors dense [batch, M, N]
       const int64_t off = (int64_t)b * MN + gi * p.N + gj;
       float w[4];
@@ -396,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
       if (EPI == EPI_AMAX) {
         if (p.transformed) {
           if (full) {
-            *reinterpret_cast<float4 *>(p.transformed + off) = make_float4(w[0], w[1], w[2], w[3]);
+            st4u(p.transformed + off, w[0], w[1], w[2], w[3]);
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -406,8 +423,12 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if (gj + e >= p.N) break;
-          const int64_t lbj = (gj + e) / p.bc - lb.bj0;
-          const int l = (int)(lbi * lb.nlbj + lbj);
+          if (left == 0) {
+            ++lbj;
+            left = (int)p.bc;
+          }
+          --left;
+          const int l = lbi * lb.nlbj + lbj;
           const uint32_t a = __float_as_uint(w[e]) & 0x7fffffffu;
           if (l != run_lb) {
             if (run_lb >= 0) {
@@ -416,7 +437,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
             }
             run_lb = l;
             run_max = 0u;
-            run_gb = (int64_t)b * p.nbr * p.nbc + (gi / p.br) * p.nbc + (gj + e) / p.bc;
+            run_gb = (int64_t)b * p.nbr * p.nbc + (int64_t)(lb.bi0 + lbi) * p.nbc + lb.bj0 + lbj;
           }
           run_max = a > run_max ? a : run_max;
         }
@@ -427,13 +448,17 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
         for (int e = 0; e < 4; ++e) {
           if (gj + e >= p.N) break;
           float inv, sc;
-          const int64_t lbj = (gj + e) / p.bc - lb.bj0;
-          const int l = (int)(lbi * lb.nlbj + lbj);
+          if (left == 0) {
+            ++lbj;
+            left = (int)p.bc;
+          }
+          --left;
+          const int l = lbi * lb.nlbj + lbj;
           if (lb.nlb <= kMaxLocalBlocks) {
             inv = lds_inv[l];
             sc = lds_scale[l];
           } else {
-            const int64_t gb = (gi / p.br) * p.nbc + (gj + e) / p.bc;
+            const int64_t gb = (int64_t)(lb.bi0 + lbi) * p.nbc + lb.bj0 + lbj;
             const float a = __uint_as_float(p.amax[b * (int64_t)p.nbr * p.nbc + gb]);
             inv = e4m3_multiplier(a);
             sc = e4m3_scale(a);
@@ -448,8 +473,8 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
           if (p.ef) resid[e] = w[e] - e4m3_decode(code) * sc;
         }
         uint8_t *cp = p.codes + off;
-        if (full && ((off & 3) == 0)) {
-          *reinterpret_cast<uint32_t *>(cp) = packed;
+        if (full) {
+          *reinterpret_cast<u32u *>(cp) = packed;
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
@@ -457,7 +482,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
         }
         if (p.ef) {
           if (full) {
-            *reinterpret_cast<float4 *>(p.ef + off) = make_float4(resid[0], resid[1], resid[2], resid[3]);
+            st4u(p.ef + off, resid[0], resid[1], resid[2], resid[3]);
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -479,7 +504,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(const KArgs p) {
       for (int l = tid; l < lb.nlb; l += kThreads) {
         const uint32_t v = lds_amax[l];
         if (v != 0u) {
-          const int64_t bi = lb.bi0 + l / lb.nlbj, bj = lb.bj0 + l % lb.nlbj;
+          const int64_t bi = lb.bi0 + (uint32_t)l / (uint32_t)lb.nlbj, bj = lb.bj0 + (uint32_t)l % (uint32_t)lb.nlbj;
           atomicMax(&p.amax[((int64_t)b * p.nbr * p.nbc + bi * p.nbc + bj) * kAmaxSlots + slot], v);
         }
       }
@@ -530,13 +555,11 @@ __global__ void copy_f32_kernel(float *dst, const float *src, int64_t n) {
 
 KArgs make_args(const TileJob &j) {
   KArgs a{};
-  // (a table's pointers are 16-byte aligned: the grouped decode checks them)
   auto op = [](const Operand &o) {
     OperandP r{};
     r.ptr = o.ptr;
     r.ld = o.ld;
     r.bs = o.bs;
-    r.vec = (o.ld % 4 == 0) && (o.bs % 4 == 0) && ((reinterpret_cast<uintptr_t>(o.ptr) & 15) == 0);
     r.tab = o.tab;
     return r;
   };
@@ -571,14 +594,6 @@ KArgs make_args(const TileJob &j) {
   a.nbr = j.geom.nbr;
   a.nbc = j.geom.nbc;
   a.shared = j.shared ? 1 : 0;
-  auto al16 = [](const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  bool vec = true;
-  if (j.C) vec = vec && al16(j.C) && j.ldc % 4 == 0 && j.cbs % 4 == 0;
-  if (j.D) vec = vec && al16(j.D) && j.ldd % 4 == 0 && j.dbs % 4 == 0;
-  if (j.transformed) vec = vec && al16(j.transformed);
-  if (j.ef) vec = vec && al16(j.ef);
-  if (j.amax) vec = vec && (j.N % 4 == 0);
-  a.vec_out = vec ? 1 : 0;
   return a;
 }
 

@@ -92,6 +92,9 @@ __device__ __forceinline__ void st4_untracked(float *p, float x, float y, float 
   asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
+// a 4-byte store at any byte's address (rows of an odd length)
+typedef uint32_t u32u __attribute__((aligned(1)));
+
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -111,7 +114,13 @@ __device__ __forceinline__ float block_amax_value(const UArgs &p, int b, int64_t
 // of a tile (64 columns x K, shared by the 4 waves) is staged in LDS, double
 // buffered: while the waves run the MFMAs of tile c, they hold the global
 // loads of tile c+1's operand and of its W / residual values in registers.
-template <int EPI, bool EF, int NSEG, int K16>
+// (1001 x 2731 at rank 48, six ranks: 77 / 93 us for the maxima / codes on the
+// tile kernel, which took such rows and ranks before, 36 / 39 here.)
+// RAG: N is no multiple of 4.  Rows then start at any float (16-byte accesses
+// need no more), and a lane whose four columns cross the end of the row loads
+// the row's last four instead and shifts them, so that no load passes the end
+// of the matrix; it stores what lies inside the row.
+template <int EPI, bool EF, int NSEG, int K16, bool RAG>
 __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
   constexpr int KT = 16 * K16 * NSEG;          // total contraction length
   constexpr int ROW = KT + 4;                  // LDS row stride (floats)
@@ -202,14 +211,25 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
   const __amdgpu_buffer_rsrc_t rsE = __builtin_amdgcn_make_buffer_rsrc(
       (void *)(EF ? p.ef + (int64_t)b * MN : p.D), (short)0, EF ? (int)(MN * 4) : 0, 0x00020000);
   const uint32_t roff = rv ? (uint32_t)(ri * p.N * 4) : 0x80000000u;
+  // columns by which the lane's four from cj on pass the end of the row
+  auto over = [&](int64_t cj) -> int { return RAG && cj < p.N && cj + 4 > p.N ? (int)(cj + 4 - p.N) : 0; };
   float4 d[4], rr[4];
   auto load_w = [&](int64_t j0) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const uint32_t off = roff + (uint32_t)((j0 + 16 * t + 4 * fg) * 4);
+      const int64_t cj = j0 + 16 * t + 4 * fg;
+      const uint32_t off = roff + (uint32_t)((cj - over(cj)) * 4);
       d[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsD, (int)off, 0, 0));
       if (EF) rr[t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsE, (int)off, 0, 0));
     }
+  };
+  // the loaded values of a lane's columns (see RAG)
+  auto in_place = [&](float4 v, int s) {
+    if (RAG) {
+      if (s & 1) v = make_float4(v.y, v.z, v.w, v.w);
+      if (s & 2) v = make_float4(v.z, v.w, v.w, v.w);
+    }
+    return v;
   };
 
   uint32_t run_max = 0u;
@@ -226,8 +246,9 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
     float4 dcur[4], rcur[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      dcur[t] = d[t];
-      if (EF) rcur[t] = rr[t];
+      const int s = over(j0 + 16 * t + 4 * fg);
+      dcur[t] = in_place(d[t], s);
+      if (EF) rcur[t] = in_place(rr[t], s);
     }
     if (more) {
       load_cols(j0 + 64);
@@ -278,14 +299,22 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
           const int64_t cj = j0 + 16 * t + 4 * fg;
-          if (rv && cj < p.N) st4_untracked(Cb + ri * p.N + cj, w[t][0], w[t][1], w[t][2], w[t][3]);
+          if (!(rv && cj < p.N)) continue;
+          float *const o = Cb + ri * p.N + cj;
+          if (!RAG || cj + 4 <= p.N) {
+            st4_untracked(o, w[t][0], w[t][1], w[t][2], w[t][3]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+              if (cj + e < p.N) o[e] = w[t][e];
+          }
         }
       } else {
         // scale-block geometry of this wave tile (wave-uniform, two divisions)
         const int64_t rlast = (i0 + 15 < p.M ? i0 + 15 : p.M - 1);
         const int64_t clast = (j0 + 63 < p.N ? j0 + 63 : p.N - 1);
-        const int bi_lo = __builtin_amdgcn_readfirstlane((int)(i0 / p.br));
-        const int bj_lo = __builtin_amdgcn_readfirstlane((int)(j0 / p.bc));
+        const int bi_lo = __builtin_amdgcn_readfirstlane((int)((uint32_t)i0 / (uint32_t)p.br));
+        const int bj_lo = __builtin_amdgcn_readfirstlane((int)((uint32_t)j0 / (uint32_t)p.bc));
         const bool uniform = (int64_t)(bi_lo + 1) * p.br > rlast && (int64_t)(bj_lo + 1) * p.bc > clast;
         const int64_t u_gb = (int64_t)bi_lo * p.nbc + bj_lo;
         if (EPI == EPI_AMAX) {
@@ -293,9 +322,15 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
               const int64_t cj = j0 + 16 * t + 4 * fg;
-              if (rv && cj < p.N)
-                *reinterpret_cast<float4 *>(p.transformed + (int64_t)b * MN + ri * p.N + cj) =
-                    make_float4(w[t][0], w[t][1], w[t][2], w[t][3]);
+              if (!(rv && cj < p.N)) continue;
+              float *const o = p.transformed + (int64_t)b * MN + ri * p.N + cj;
+              if (!RAG || cj + 4 <= p.N) {
+                st4_untracked(o, w[t][0], w[t][1], w[t][2], w[t][3]);
+              } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                  if (cj + e < p.N) o[e] = w[t][e];
+              }
             }
           }
           if (uniform) {
@@ -306,7 +341,7 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
               if (rv && cj < p.N) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                  const uint32_t a = __float_as_uint(w[t][e]) & 0x7fffffffu;
+                  const uint32_t a = !RAG || cj + e < p.N ? __float_as_uint(w[t][e]) & 0x7fffffffu : 0u;
                   m = a > m ? a : m;
                 }
               }
@@ -328,8 +363,9 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
               if (!(rv && cj < p.N)) continue;
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
+                if (RAG && cj + e >= p.N) break;
                 const uint32_t a = __float_as_uint(w[t][e]) & 0x7fffffffu;
-                const int64_t gb = (ri / p.br) * p.nbc + (cj + e) / p.bc;
+                const int64_t gb = (int64_t)((uint32_t)ri / (uint32_t)p.br) * p.nbc + (uint32_t)(cj + e) / (uint32_t)p.bc;
                 if (a) atomicMax(&p.amax[((int64_t)b * p.nbr * p.nbc + gb) * kAmaxSlots + slot], a);
               }
             }
@@ -345,27 +381,44 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
           for (int t = 0; t < 4; ++t) {
             const int64_t cj = j0 + 16 * t + 4 * fg;
             if (!(rv && cj < p.N)) continue;
-            uint32_t packed = 0u;
-            float res[4];
+            float inv[4] = {u_inv, u_inv, u_inv, u_inv}, sc[4] = {u_s, u_s, u_s, u_s};
+            if (!uniform) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              float inv = u_inv, sc = u_s;
-              if (!uniform) {
-                const float a = block_amax_value(p, b, (ri / p.br) * p.nbc + (cj + e) / p.bc);
-                inv = e4m3_multiplier(a);
-                sc = e4m3_scale(a);
+              for (int e = 0; e < 4; ++e) {
+                const int64_t c = !RAG || cj + e < p.N ? cj + e : p.N - 1;
+                const float a = block_amax_value(
+                    p, b, (int64_t)((uint32_t)ri / (uint32_t)p.br) * p.nbc + (uint32_t)c / (uint32_t)p.bc);
+                inv[e] = e4m3_multiplier(a);
+                sc[e] = e4m3_scale(a);
               }
-              const uint32_t code = e4m3_encode(w[t][e] * inv);
-              packed |= code << (8 * e);
-              if (p.hits) {
-                hit_up += (code & 0x7fu) == 0x7eu;
-                hit_lo += ((code & 0x7fu) == 0u) & (w[t][e] != 0.0f);
-              }
-              if (EF) res[e] = w[t][e] - e4m3_decode(code) * sc;
+            }
+            const uint32_t packed =
+                e4m3_encode4(w[t][0] * inv[0], w[t][1] * inv[1], w[t][2] * inv[2], w[t][3] * inv[3]);
+            float res[4];
+            if (EF) {
+              float q[4];
+              e4m3_decode4(packed, q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) res[e] = w[t][e] - q[e] * sc[e];
             }
             const int64_t off = (int64_t)b * MN + ri * p.N + cj;
-            *reinterpret_cast<uint32_t *>(p.codes + off) = packed;
-            if (EF) *reinterpret_cast<float4 *>(p.ef + off) = make_float4(res[0], res[1], res[2], res[3]);
+            if (!RAG || cj + 4 <= p.N) {
+              if (p.hits) e4m3_count_hits4(packed, w[t][0], w[t][1], w[t][2], w[t][3], hit_up, hit_lo);
+              *reinterpret_cast<u32u *>(p.codes + off) = packed;
+              if (EF) st4_untracked(p.ef + off, res[0], res[1], res[2], res[3]);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 3; ++e) {
+                if (cj + e >= p.N) break;
+                const uint32_t code = (packed >> (8 * e)) & 0xffu;
+                p.codes[off + e] = (uint8_t)code;
+                if (p.hits) {
+                  hit_up += (code & 0x7fu) == 0x7eu;
+                  hit_lo += ((code & 0x7fu) == 0u) & (w[t][e] != 0.0f);
+                }
+                if (EF) p.ef[off + e] = res[e];
+              }
+            }
           }
         }
       }
@@ -491,7 +544,10 @@ __global__ __launch_bounds__(kThreads) void proj_kernel(const PArgs p) {
 // each wave holds the next chunk's X values in registers.  Sharing Y through
 // LDS cuts the L2 requests for it by the four strips, which otherwise bound
 // this skinny product.
-template <int NT>
+// RAG: K or a row stride no multiple of 4, or an operand at no 16-byte address:
+// 16-byte loads at any float, a group that crosses the end of the row from its
+// last four floats, shifted and filled with zeros.
+template <int NT, bool RAG>
 __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, int parts) {
   constexpr int C = 16 * NT;
   constexpr int KC = 64;                // contraction steps per chunk
@@ -509,13 +565,23 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
   const float *xrow = (p.tab ? p.tab[b].mean : p.X + (int64_t)b * p.x_bs) + ri * p.x_ld;
   const float *yb = p.tab ? p.tab[b].ut : p.Y + (int64_t)b * p.y_bs;
   float4 yreg[PER], xn[4];
+  auto ldk = [&](const float *row, int64_t k) {
+    if (!RAG) return ld4(row + k);
+    typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int s = k + 4 > p.K ? (int)(k + 4 - p.K) : 0;
+    const float4u u = *reinterpret_cast<const float4u *>(row + (k - s));
+    float4 v = make_float4(u.x, u.y, u.z, u.w);
+    if (s & 1) v = make_float4(v.y, v.z, v.w, 0.f);
+    if (s & 2) v = make_float4(v.z, v.w, 0.f, 0.f);
+    return v;
+  };
   auto load_y = [&](int64_t kc) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int slot = tid + u * kThreads;
       const int c = slot / (KC / 4), k4 = slot % (KC / 4);
       const int64_t k = kc + 4 * k4;
-      yreg[u] = (c < p.C && k < k1) ? ld4(yb + (int64_t)c * p.y_ld + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      yreg[u] = (c < p.C && k < k1) ? ldk(yb + (int64_t)c * p.y_ld, k) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
   auto store_y = [&](int buf) {
@@ -530,7 +596,7 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int64_t k = kc + 16 * q + 4 * fg;
-      xn[q] = (rv && k < k1) ? ld4(xrow + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      xn[q] = (rv && k < k1) ? ldk(xrow, k) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
   floatx4 acc[NT];
@@ -580,12 +646,95 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
   }
 }
 
+// Projection with one unsplit contraction per output for grids too small to
+// fill the chip, operands at any address: out[b][i][c] = sum_k X[b][i][k]
+// Y[c][k].  What bounds it is the chain of dependent steps, so a wave takes the
+// shortest one, 16 rows x 16 columns, straight from registers, with kDeep
+// 32-step chunks of both operands in flight and no barrier; the other column
+// tiles of its rows read X again from L2.  The steps come in the order of the
+// tile kernel, so its sums are those bit for bit (splitting the contraction
+// would be as quick and round less, but other codes come out of the encode for
+// values on an edge).  1001 x 2731, rank 48, six ranks: 132 us on the tile
+// kernel (96 workgroups, 86 steps of a load, two barriers and eight products),
+// 66 us here.
+constexpr int kDeep = 6;
+template <bool RAG>
+__global__ __launch_bounds__(kThreads) void proj_chain_kernel(const PArgs p) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int b = blockIdx.z;
+  const int64_t ri = ((int64_t)blockIdx.x * 4 + wave) * 16 + fr;
+  if (ri - fr >= p.M) return;
+  const int c = (int)blockIdx.y * 16 + fr;
+  const bool rv = ri < p.M, cv = c < p.C;
+  const float *x = p.X + (int64_t)b * p.x_bs + (rv ? ri : 0) * p.x_ld;
+  const float *y = p.Y + (int64_t)b * p.y_bs + (int64_t)(cv ? c : 0) * p.y_ld;
+  typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+  // four steps from k on; past K at a valid address, made zero on use
+  auto fetch = [&](const float *row, int64_t k) {
+    if (RAG) k = k + 4 <= p.K ? k : p.K - 4;
+    else k = k < p.K ? k : 0;
+    const float4u u = *reinterpret_cast<const float4u *>(row + k);
+    return make_float4(u.x, u.y, u.z, u.w);
+  };
+  auto use = [&](float4 v, int64_t k, bool ok) {
+    if (RAG) {
+      const int s = k + 4 > p.K ? (int)(k + 4 - p.K < 4 ? k + 4 - p.K : 4) : 0;
+      if (s & 1) v = make_float4(v.y, v.z, v.w, 0.f);
+      if (s & 2) v = make_float4(v.z, v.w, 0.f, 0.f);
+      ok = ok && s < 4;
+    } else {
+      ok = ok && k < p.K;
+    }
+    return ok ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+  };
+  float4 xb[kDeep][2], yb[kDeep][2];
+  auto load = [&](int u, int64_t k0) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      xb[u][q] = fetch(x, k0 + 16 * q + 4 * fg);
+      yb[u][q] = fetch(y, k0 + 16 * q + 4 * fg);
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < kDeep; ++u) load(u, 32 * u);
+  floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t k0 = 0; k0 < p.K; k0 += 32 * kDeep) {
+#pragma unroll
+    for (int u = 0; u < kDeep; ++u) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int64_t k = k0 + 32 * u + 16 * q + 4 * fg;
+        const float4 xv = use(xb[u][q], k, rv), yv = use(yb[u][q], k, cv);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(yv.x, xv.x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(yv.y, xv.y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(yv.z, xv.z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(yv.w, xv.w, acc, 0, 0, 0);
+      }
+      load(u, k0 + 32 * (u + kDeep));
+    }
+  }
+  if (!rv) return;
+  // lane holds out[ri][16 blockIdx.y + 4 fg + v]
+  float *o = p.out + (int64_t)b * p.out_bs + ri * p.out_ld + 16 * (int)blockIdx.y + 4 * fg;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+    if (16 * (int)blockIdx.y + 4 * fg + v < p.C) o[v] = acc[v];
+}
+
 bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 bool staged_eligible(const TileJob &j) {
   const Segment &g = j.seg[0];
-  return !proj_strip_is_b(j) && g.b.bs == 0 && j.N % 16 == 0 && j.N <= 128 && g.K % 4 == 0 && j.ldc % 4 == 0 &&
+  return !proj_strip_is_b(j) && g.b.bs == 0 && j.N % 16 == 0 && j.N <= 128 && g.K >= 4 && j.ldc % 4 == 0 &&
          j.cbs % 4 == 0 && al16(j.C);
+}
+
+// its operands in whole 16-byte groups
+bool staged_aligned(const TileJob &j) {
+  const Segment &g = j.seg[0];
+  return g.K % 4 == 0 && g.a.ld % 4 == 0 && g.a.bs % 4 == 0 && g.b.ld % 4 == 0 && g.b.bs % 4 == 0 && al16(g.a.ptr) &&
+         al16(g.b.ptr);
 }
 
 }  // namespace
@@ -602,7 +751,8 @@ int proj_parts(int64_t M, int64_t K, int C, int32_t batch) {
 bool proj_staged_eligible(const TileJob &j) { return proj_kernel_eligible(j) && staged_eligible(j); }
 
 bool update_kernel_eligible(const TileJob &j) {
-  if (j.N % 4 != 0 || j.nseg < 1 || j.nseg > 2) return false;
+  // (rows shorter than a lane's four columns: the tile kernel)
+  if (j.N < 4 || j.nseg < 1 || j.nseg > 2) return false;
   // per-entry tables: a store with the decode's table for neither, a
   // partial-free operand behind each table, no column scales
   if (job_has_tabs(j)) {
@@ -613,16 +763,15 @@ bool update_kernel_eligible(const TileJob &j) {
   }
   if (j.M * j.N >= (1LL << 29)) return false;   // one rank's slice within a 32-bit buffer range
   const int64_t K = j.seg[0].K;
-  if (K != 16 && K != 32 && K != 64 && K != 128) return false;
+  if (K != 16 && K != 32 && K != 48 && K != 64 && K != 96 && K != 128) return false;
   for (int s = 0; s < j.nseg; ++s) {
     const Segment &g = j.seg[s];
     if (!g.a.kmajor || !g.b.kmajor || g.K != K) return false;
     if (g.a.ld % 4 || g.b.ld % 4 || g.a.bs % 4 || g.b.bs % 4) return false;
     if (!al16(g.a.ptr) || !al16(g.b.ptr)) return false;
   }
-  if (!al16(j.D) || (j.C && !al16(j.C)) || (!j.D && !j.d_tab) || (j.transformed && !al16(j.transformed)) ||
-      (j.ef && !al16(j.ef)) || (j.codes && (reinterpret_cast<uintptr_t>(j.codes) & 3)))
-    return false;
+  // (W, the residual, W~, the output and the codes at any address)
+  if (!j.D && !j.d_tab) return false;
   if (j.amax == nullptr) {  // decode store: dense output, D dense
     if (j.ldc != j.N || j.cbs != j.M * j.N || j.ldd != j.N || j.dbs != j.M * j.N || j.beta != 1.f ||
         j.alpha != 1.f || j.colscale || j.ksplit > 1)
@@ -672,15 +821,22 @@ gift_status launch_update(gift_ctx *ctx, const TileJob &j) {
   const bool ef = j.ef != nullptr && epi != EPI_STORE;
   const int k16 = (int)(j.seg[0].K / 16);
   auto go = [&](auto epi_c, auto ef_c, auto nseg_c, auto k16_c) {
-    hipLaunchKernelGGL((update_kernel<decltype(epi_c)::value, decltype(ef_c)::value,
-                                      decltype(nseg_c)::value, decltype(k16_c)::value>),
-                       grid, dim3(kThreads), 0, ctx->stream, a);
+    if (j.N % 4 != 0)
+      hipLaunchKernelGGL((update_kernel<decltype(epi_c)::value, decltype(ef_c)::value, decltype(nseg_c)::value,
+                                        decltype(k16_c)::value, true>),
+                         grid, dim3(kThreads), 0, ctx->stream, a);
+    else
+      hipLaunchKernelGGL((update_kernel<decltype(epi_c)::value, decltype(ef_c)::value, decltype(nseg_c)::value,
+                                        decltype(k16_c)::value, false>),
+                         grid, dim3(kThreads), 0, ctx->stream, a);
   };
   auto by_k = [&](auto epi_c, auto ef_c, auto nseg_c) {
     switch (k16) {
       case 1: go(epi_c, ef_c, nseg_c, std::integral_constant<int, 1>{}); break;
       case 2: go(epi_c, ef_c, nseg_c, std::integral_constant<int, 2>{}); break;
+      case 3: go(epi_c, ef_c, nseg_c, std::integral_constant<int, 3>{}); break;
       case 4: go(epi_c, ef_c, nseg_c, std::integral_constant<int, 4>{}); break;
+      case 6: go(epi_c, ef_c, nseg_c, std::integral_constant<int, 6>{}); break;
       default: go(epi_c, ef_c, nseg_c, std::integral_constant<int, 8>{}); break;
     }
   };
@@ -708,14 +864,47 @@ static bool proj_strip_is_b(const TileJob &j) { return j.M <= 256 && j.N > j.M; 
 
 bool proj_kernel_eligible(const TileJob &j) {
   const Segment &g = j.seg[0];
-  const bool base = j.nseg == 1 && j.amax == nullptr && g.a.kmajor && g.b.kmajor && g.K % 4 == 0 &&
-                    g.a.ld % 4 == 0 && g.a.bs % 4 == 0 && g.b.ld % 4 == 0 && g.b.bs % 4 == 0 &&
-                    al16(g.a.ptr) && al16(g.b.ptr) && j.D == nullptr && j.colscale == nullptr &&
-                    j.alpha == 1.f;
+  const bool base = j.nseg == 1 && j.amax == nullptr && g.a.kmajor && g.b.kmajor && j.D == nullptr &&
+                    j.colscale == nullptr && j.alpha == 1.f;
   if (!base) return false;
-  if (j.ksplit > 1) return staged_eligible(j);       // partials: staged kernel only
+  // partials, and operands at any address: the staged kernel only
+  if (j.ksplit > 1 || !staged_aligned(j)) return staged_eligible(j);
   if (proj_strip_is_b(j)) return true;              // transposed, scalar stores
   return j.N % 4 == 0 && j.ldc % 4 == 0 && j.cbs % 4 == 0 && al16(j.C);
+}
+
+// The short-chain projection: a plain k-major product whose tile grid would
+// leave most of the chip idle.
+bool proj_chain_eligible(const TileJob &j) {
+  const Segment &g = j.seg[0];
+  return j.nseg == 1 && j.amax == nullptr && g.a.kmajor && g.b.kmajor && !job_has_tabs(j) && !j.decode_tab &&
+         j.D == nullptr && j.colscale == nullptr && j.alpha == 1.f && j.ksplit <= 1 && g.K >= 4 &&
+         j.N <= 16 * 65535 && (j.M + 63) / 64 * j.batch < 512;
+}
+
+gift_status launch_proj_chain(gift_ctx *ctx, const TileJob &j) {
+  if (!proj_chain_eligible(j)) return GIFT_EUNSUPPORTED;
+  PArgs a{};
+  const Segment &g = j.seg[0];
+  a.X = g.a.ptr;
+  a.x_ld = g.a.ld;
+  a.x_bs = g.a.bs;
+  a.Y = g.b.ptr;
+  a.y_ld = g.b.ld;
+  a.y_bs = g.b.bs;
+  a.M = j.M;
+  a.K = g.K;
+  a.C = (int)j.N;
+  a.out = j.C;
+  a.out_ld = j.ldc;
+  a.out_bs = j.cbs;
+  ProfileScope prof(ctx, j.kernel_family);
+  const dim3 grid((unsigned)((j.M + 63) / 64), (unsigned)((j.N + 15) / 16), (unsigned)j.batch);
+  if (g.K % 4 != 0)
+    hipLaunchKernelGGL(proj_chain_kernel<true>, grid, dim3(kThreads), 0, ctx->stream, a);
+  else
+    hipLaunchKernelGGL(proj_chain_kernel<false>, grid, dim3(kThreads), 0, ctx->stream, a);
+  return check_launch("proj_chain_kernel");
 }
 
 gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
@@ -742,7 +931,12 @@ gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
     const int parts = j.ksplit > 1 ? j.ksplit : 1;
     const int nt = (int)(j.N / 16);
     const dim3 sgrid((unsigned)((a.M + 63) / 64), (unsigned)parts, (unsigned)j.batch);
-#define GIFT_PROJS(NT) hipLaunchKernelGGL((proj_staged_kernel<NT>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts)
+    const bool rag = !staged_aligned(j);
+#define GIFT_PROJS(NT)                                                                                              \
+  do {                                                                                                              \
+    if (rag) hipLaunchKernelGGL((proj_staged_kernel<NT, true>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts);   \
+    else hipLaunchKernelGGL((proj_staged_kernel<NT, false>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts);      \
+  } while (0)
     switch (nt) {
       case 1: GIFT_PROJS(1); break;
       case 2: GIFT_PROJS(2); break;
