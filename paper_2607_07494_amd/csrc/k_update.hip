@@ -430,6 +430,143 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const UArgs p) {
   if (EPI == EPI_QUANT && p.hits) e4m3_flush_hits(p.hits + 2 * (int64_t)b, hit_up, hit_lo);
 }
 
+// The inverse transform's update (EPI_STORE, one segment) for grids that fill
+// the chip with larger workgroups: 128 rows (32 per wave) x `units` 64-column
+// tiles.  The column operand's tile is staged for twice the rows and every LDS
+// fragment feeds two products, and the row operand is loaded once per `units`
+// tiles.  The sums are those of update_kernel in the same order.
+// 8 x 4608 x 1536 at rank 128: update_kernel 301 us (the 64-row workgroup moves
+// twice its W tile in column operand, with a barrier per tile), 233 here (62
+// TFLOP/s; the FP32 matrix cores do 153 in a large product).
+template <int K16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void update_store_kernel(
+    const UArgs p, int units) {
+  constexpr int KT = 16 * K16;
+  constexpr int ROW = KT + 4;
+  constexpr int PER = 64 * KT / 4 / kThreads;
+  __shared__ __attribute__((aligned(16))) float lds[2][64 * ROW];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int fr = lane & 15, fg = lane >> 4;
+  const int64_t lin = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+  const int64_t wg_tile = xcd_tile(lin, (int64_t)gridDim.x * gridDim.y * gridDim.z);
+  const int64_t tx = wg_tile % gridDim.x, ty = (wg_tile / gridDim.x) % gridDim.y;
+  const int b = (int)(wg_tile / ((int64_t)gridDim.x * gridDim.y));
+  const int64_t MN = p.M * p.N;
+  const int64_t c_begin = tx * 64 * units;
+  const int64_t left = (p.N - c_begin + 63) / 64;
+  const int ntiles = (int)(left < units ? left : units);
+  int64_t ri[2];
+  bool rv[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    ri[g] = ty * 128 + wave * 32 + 16 * g + fr;
+    rv[g] = ri[g] < p.M;
+  }
+  const float *const colb = p.tab ? p.tab[b].uci : p.seg[0].col + (int64_t)b * p.seg[0].col_bs;
+  float4 creg[PER];
+  auto load_cols = [&](int64_t j0) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int slot = tid + u * kThreads;
+      const int64_t cj = j0 + slot / (KT / 4);
+      creg[u] = ld4(colb + (cj < p.N ? cj : 0) * p.seg[0].col_ld + 4 * (slot % (KT / 4)));
+    }
+  };
+  auto store_cols = [&](int buf, int64_t j0) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int slot = tid + u * kThreads;
+      const int col = slot / (KT / 4), kq = slot % (KT / 4);
+      *reinterpret_cast<float4 *>(&lds[buf][col * ROW + 4 * kq]) =
+          j0 + col < p.N ? creg[u] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  };
+  const float *const Db = p.tab ? p.tab[b].mean : p.D + (int64_t)b * MN;
+  float *const Cb = p.tab ? p.tab[b].out : p.C + (int64_t)b * MN;
+  const __amdgpu_buffer_rsrc_t rsD =
+      __builtin_amdgcn_make_buffer_rsrc((void *)Db, (short)0, (int)(MN * 4), 0x00020000);
+  uint32_t roff[2];
+#pragma unroll
+  for (int g = 0; g < 2; ++g) roff[g] = rv[g] ? (uint32_t)(ri[g] * p.N * 4) : 0x80000000u;
+  float4 d[2][4];
+  auto load_w = [&](int64_t j0) {
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        d[g][t] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                 rsD, (int)(roff[g] + (uint32_t)((j0 + 16 * t + 4 * fg) * 4)), 0, 0));
+  };
+  load_cols(c_begin);
+  // the row operand, its split-K partials summed in order
+  float4 bfr[2][K16];
+  const int np = p.seg[0].row_parts;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const float *base = p.seg[0].row + (int64_t)b * np * p.seg[0].row_bs + (rv[g] ? ri[g] : 0) * p.seg[0].row_ld + 4 * fg;
+#pragma unroll
+    for (int q = 0; q < K16; ++q) bfr[g][q] = ld4(base + 16 * q);
+    for (int z = 1; z < np; ++z) {
+      float4 u[K16];
+#pragma unroll
+      for (int q = 0; q < K16; ++q) u[q] = ld4(base + (int64_t)z * p.seg[0].row_bs + 16 * q);
+#pragma unroll
+      for (int q = 0; q < K16; ++q) {
+        bfr[g][q].x += u[q].x;
+        bfr[g][q].y += u[q].y;
+        bfr[g][q].z += u[q].z;
+        bfr[g][q].w += u[q].w;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < K16; ++q)
+      if (!rv[g]) bfr[g][q] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  load_w(c_begin);
+  store_cols(0, c_begin);
+  __syncthreads();
+  for (int ct = 0; ct < ntiles; ++ct) {
+    const int buf = ct & 1;
+    const int64_t j0 = c_begin + 64 * ct;
+    const bool more = ct + 1 < ntiles;
+    if (more) load_cols(j0 + 64);
+    floatx4 acc[2][4];
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) acc[g][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < K16; ++q) {
+      float4 a[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        a[t] = *reinterpret_cast<const float4 *>(&lds[buf][(16 * t + fr) * ROW + 16 * q + 4 * fg]);
+#define GIFT_STEP(E)                                  \
+  _Pragma("unroll") for (int g = 0; g < 2; ++g)       \
+  _Pragma("unroll") for (int t = 0; t < 4; ++t)       \
+    acc[g][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t].E, bfr[g][q].E, acc[g][t], 0, 0, 0)
+      GIFT_STEP(x);
+      GIFT_STEP(y);
+      GIFT_STEP(z);
+      GIFT_STEP(w);
+#undef GIFT_STEP
+    }
+    if (more) store_cols(buf ^ 1, j0 + 64);
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int64_t cj = j0 + 16 * t + 4 * fg;
+        if (rv[g] && cj < p.N)
+          st4_untracked(Cb + ri[g] * p.N + cj, d[g][t].x + acc[g][t][0], d[g][t].y + acc[g][t][1],
+                        d[g][t].z + acc[g][t][2], d[g][t].w + acc[g][t][3]);
+      }
+    if (more) load_w(j0 + 64);
+    __syncthreads();
+  }
+}
+
 struct PArgs {
   const float *X;     // [batch][M][K]
   int64_t x_ld, x_bs;
@@ -547,8 +684,13 @@ __global__ __launch_bounds__(kThreads) void proj_kernel(const PArgs p) {
 // RAG: K or a row stride no multiple of 4, or an operand at no 16-byte address:
 // 16-byte loads at any float, a group that crosses the end of the row from its
 // last four floats, shifted and filled with zeros.
-template <int NT, bool RAG>
-__global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, int parts) {
+// RG 16-row strips per wave: two when the grid still fills the chip, so that
+// each staged chunk of Y and each LDS fragment serves twice the rows.  blocks:
+// blocks of 16 NT columns, for the refresh's Q A at k > 128 (k = 256, six
+// factors of 4096: 1047 us on proj_kernel, whose waves read Q from L2 for 16
+// rows each, 617 here).
+template <int NT, bool RAG, int RG>
+__global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, int parts, int blocks) {
   constexpr int C = 16 * NT;
   constexpr int KC = 64;                // contraction steps per chunk
   constexpr int LD = KC + 4;            // padded LDS row (floats)
@@ -556,15 +698,23 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
   __shared__ __attribute__((aligned(16))) float ys[2][C * LD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int fr = lane & 15, fg = lane >> 4;
-  const int b = blockIdx.z, z = blockIdx.y;
-  const int64_t ri = ((int64_t)blockIdx.x * 4 + wave) * 16 + fr;
-  const bool rv = ri < p.M;
+  const int b = blockIdx.z, z = blockIdx.y / blocks, c0 = (int)blockIdx.y % blocks * C;
+  int64_t ri[RG];
+  bool rv[RG];
+#pragma unroll
+  for (int g = 0; g < RG; ++g) {
+    ri[g] = (((int64_t)blockIdx.x * 4 + wave) * RG + g) * 16 + fr;
+    rv[g] = ri[g] < p.M;
+  }
   const int64_t kper = ((p.K + parts - 1) / parts + KC - 1) / KC * KC;
   const int64_t k0 = z * kper, k1 = k0 + kper < p.K ? k0 + kper : p.K;
   const int nchunks = k1 > k0 ? (int)((k1 - k0 + KC - 1) / KC) : 0;
-  const float *xrow = (p.tab ? p.tab[b].mean : p.X + (int64_t)b * p.x_bs) + ri * p.x_ld;
-  const float *yb = p.tab ? p.tab[b].ut : p.Y + (int64_t)b * p.y_bs;
-  float4 yreg[PER], xn[4];
+  const float *const xb = p.tab ? p.tab[b].mean : p.X + (int64_t)b * p.x_bs;
+  const float *xrow[RG];
+#pragma unroll
+  for (int g = 0; g < RG; ++g) xrow[g] = xb + (rv[g] ? ri[g] : 0) * p.x_ld;
+  const float *const yb = (p.tab ? p.tab[b].ut : p.Y + (int64_t)b * p.y_bs) + (int64_t)c0 * p.y_ld;
+  float4 yreg[PER], xn[RG][4];
   auto ldk = [&](const float *row, int64_t k) {
     if (!RAG) return ld4(row + k);
     typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -581,7 +731,7 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
       const int slot = tid + u * kThreads;
       const int c = slot / (KC / 4), k4 = slot % (KC / 4);
       const int64_t k = kc + 4 * k4;
-      yreg[u] = (c < p.C && k < k1) ? ldk(yb + (int64_t)c * p.y_ld, k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      yreg[u] = (c0 + c < p.C && k < k1) ? ldk(yb + (int64_t)c * p.y_ld, k) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
   auto store_y = [&](int buf) {
@@ -594,14 +744,18 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
   };
   auto load_x = [&](int64_t kc) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t k = kc + 16 * q + 4 * fg;
-      xn[q] = (rv && k < k1) ? ldk(xrow, k) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  };
-  floatx4 acc[NT];
+    for (int g = 0; g < RG; ++g)
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < 4; ++q) {
+        const int64_t k = kc + 16 * q + 4 * fg;
+        xn[g][q] = (rv[g] && k < k1) ? ldk(xrow[g], k) : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+  };
+  floatx4 acc[RG][NT];
+#pragma unroll
+  for (int g = 0; g < RG; ++g)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[g][t] = floatx4{0.f, 0.f, 0.f, 0.f};
   if (nchunks > 0) {
     load_y(k0);
     load_x(k0);
@@ -610,9 +764,11 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
   __syncthreads();
   for (int ch = 0; ch < nchunks; ++ch) {
     const int buf = ch & 1;
-    float4 xc[4];
+    float4 xc[RG][4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) xc[q] = xn[q];
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) xc[g][q] = xn[g][q];
     const bool more = ch + 1 < nchunks;
     if (more) {
       load_y(k0 + (int64_t)(ch + 1) * KC);
@@ -624,25 +780,38 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
 #pragma unroll
       for (int t = 0; t < NT; ++t)
         ya[t] = *reinterpret_cast<const float4 *>(&ys[buf][(16 * t + fr) * LD + 16 * q + 4 * fg]);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[t].x, xc[q].x, acc[t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[t].y, xc[q].y, acc[t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[t].z, xc[q].z, acc[t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[t].w, xc[q].w, acc[t], 0, 0, 0);
+#define GIFT_STEP(E)                                  \
+  _Pragma("unroll") for (int g = 0; g < RG; ++g)      \
+  _Pragma("unroll") for (int t = 0; t < NT; ++t)      \
+    acc[g][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(ya[t].E, xc[g][q].E, acc[g][t], 0, 0, 0)
+      GIFT_STEP(x);
+      GIFT_STEP(y);
+      GIFT_STEP(z);
+      GIFT_STEP(w);
+#undef GIFT_STEP
     }
     if (more) store_y(buf ^ 1);
     __syncthreads();
   }
-  if (!rv) return;
-  // lane holds part z of out[ri][16t + 4fg + v]
-  float *ob = p.out + ((int64_t)b * parts + z) * p.out_bs + ri * p.out_ld;
+  // lane holds part z of out[ri][c0 + 16t + 4fg + v]
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int c = 16 * t + 4 * fg;
-    if (c < p.C) *reinterpret_cast<float4 *>(ob + c) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+  for (int g = 0; g < RG; ++g) {
+    if (!rv[g]) continue;
+    if (p.out_t) {   // one part: 16 lanes of equal fg write 16 consecutive rows of a column
+      float *ob = p.out + (int64_t)b * p.out_bs + ri[g];
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) ob[(int64_t)(c0 + 16 * t + 4 * fg + v) * p.out_ld] = acc[g][t][v];
+      continue;
+    }
+    float *ob = p.out + ((int64_t)b * parts + z) * p.out_bs + ri[g] * p.out_ld + c0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = 16 * t + 4 * fg;
+      if (c0 + c < p.C)
+        *reinterpret_cast<float4 *>(ob + c) = make_float4(acc[g][t][0], acc[g][t][1], acc[g][t][2], acc[g][t][3]);
+    }
   }
 }
 
@@ -817,6 +986,25 @@ gift_status launch_update(gift_ctx *ctx, const TileJob &j) {
   ProfileScope prof(ctx, j.kernel_family);
   dim3 grid((unsigned)((j.N + kColsPerUnit - 1) / kColsPerUnit), (unsigned)((j.M + 63) / 64),
             (unsigned)j.batch);
+  // large stores (the inverse transform): 128-row workgroups once they fill
+  // the chip's 512 slots (two per CU), over four or eight tiles while the grid
+  // then holds two rounds (8 x 4608 x 1536, rank 128, at 2 / 4 / 8 tiles: 273 /
+  // 237 / 232 us; 12 x 1024 x 2816, rank 64: 142 / 125 / 127)
+  if (!j.amax && j.nseg == 1 && j.N % 4 == 0 && !j.d_tab && !j.seg[0].a.tab && !j.seg[0].b.tab &&
+      (j.seg[0].K == 64 || j.seg[0].K == 128)) {
+    const int64_t rows = (j.M + 127) / 128 * j.batch, tiles = (j.N + 63) / 64;
+    int units = 8;
+    while (units > 2 && rows * ((tiles + units - 1) / units) < 1024) units /= 2;
+    const int64_t cols = (tiles + units - 1) / units;
+    if (rows * cols >= 512) {
+      const dim3 sgrid((unsigned)cols, (unsigned)((j.M + 127) / 128), (unsigned)j.batch);
+      if (j.seg[0].K == 64)
+        hipLaunchKernelGGL(update_store_kernel<4>, sgrid, dim3(kThreads), 0, ctx->stream, a, units);
+      else
+        hipLaunchKernelGGL(update_store_kernel<8>, sgrid, dim3(kThreads), 0, ctx->stream, a, units);
+      return check_launch("update_store_kernel");
+    }
+  }
   const int epi = j.amax == nullptr ? EPI_STORE : (j.codes == nullptr ? EPI_AMAX : EPI_QUANT);
   const bool ef = j.ef != nullptr && epi != EPI_STORE;
   const int k16 = (int)(j.seg[0].K / 16);
@@ -927,15 +1115,26 @@ gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
   a.out_t = tr ? 1 : 0;
   a.tab = j.decode_tab;
   ProfileScope prof(ctx, j.kernel_family);
-  if (staged_eligible(j)) {
+  // (the transposed form, the refresh's Q A at k > 128, in blocks of equal width)
+  const bool staged_t = tr && j.ksplit <= 1 && staged_aligned(j) && a.C > 128 && a.C % 16 == 0 &&
+                        (a.C / 16) % ((a.C + 127) / 128) == 0;
+  if (staged_eligible(j) || staged_t) {
     const int parts = j.ksplit > 1 ? j.ksplit : 1;
-    const int nt = (int)(j.N / 16);
-    const dim3 sgrid((unsigned)((a.M + 63) / 64), (unsigned)parts, (unsigned)j.batch);
+    const int blocks = staged_t ? (a.C + 127) / 128 : 1;
+    const int nt = a.C / 16 / blocks;
     const bool rag = !staged_aligned(j);
-#define GIFT_PROJS(NT)                                                                                              \
-  do {                                                                                                              \
-    if (rag) hipLaunchKernelGGL((proj_staged_kernel<NT, true>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts);   \
-    else hipLaunchKernelGGL((proj_staged_kernel<NT, false>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts);      \
+    // 128-row workgroups once they fill the chip's slots (two per CU)
+    const bool two = !rag && (a.M + 127) / 128 * parts * blocks * j.batch >= 512;
+    const int rows = two ? 128 : 64;
+    const dim3 sgrid((unsigned)((a.M + rows - 1) / rows), (unsigned)(parts * blocks), (unsigned)j.batch);
+#define GIFT_PROJS(NT)                                                                                             \
+  do {                                                                                                             \
+    if (rag)                                                                                                       \
+      hipLaunchKernelGGL((proj_staged_kernel<NT, true, 1>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks); \
+    else if (two)                                                                                                  \
+      hipLaunchKernelGGL((proj_staged_kernel<NT, false, 2>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks); \
+    else                                                                                                           \
+      hipLaunchKernelGGL((proj_staged_kernel<NT, false, 1>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks); \
   } while (0)
     switch (nt) {
       case 1: GIFT_PROJS(1); break;
