@@ -293,7 +293,7 @@ int small_split(int64_t M, int64_t Nc, int64_t batch, int64_t K) {
 
 gift_status plan_low_rank(gift_ctx *ctx, const gift_factor *f, const float *W, int32_t N,
                           int64_t m, int64_t n, bool inverse, char *ws, size_t *used,
-                          LowRankPlan *plan) {
+                          LowRankPlan *plan, bool images = true) {
   const Side &A = f->A;
   const Side &G = f->G;
   const bool useA = side_in(f->sides, GIFT_SIDE_INPUT) && A.r > 0;
@@ -366,11 +366,12 @@ gift_status plan_low_rank(gift_ctx *ctx, const gift_factor *f, const float *W, i
     Kpart = reinterpret_cast<float *>(ws + off);
     off += a256(sizeof(float) * N * ksplit_k * G.r * A.r);
   }
-  // the forward update's column operands as the sweep kernel's LDS images:
+  // the forward update's column operands as the sweep kernel's LDS images
+  // (`images`: false for MXFP4, whose update reads the operands themselves):
   // input side alone, C_A U_A^T (shared); both sides at one rank, Q of each
   // rank and U_A^T (shared)
-  const bool two_img = !inverse && useA && useG && A.r == G.r && lr_col_image_bytes(n, A.r) > 0;
-  const size_t img_bytes = !inverse && useA && (!useG || two_img) ? lr_col_image_bytes(n, A.r) : 0;
+  const bool two_img = images && !inverse && useA && useG && A.r == G.r && lr_col_image_bytes(n, A.r) > 0;
+  const size_t img_bytes = images && !inverse && useA && (!useG || two_img) ? lr_col_image_bytes(n, A.r) : 0;
   const size_t qimg_bytes = two_img ? lr_col_image_bytes(n, G.r) : 0;
   void *img = nullptr, *qimg = nullptr;
   if (img_bytes) {
@@ -1233,11 +1234,11 @@ gift_status gift_encode_mxfp4(gift_ctx *ctx, const gift_factor *f, const float *
     } else {
       LowRankPlan plan;
       size_t bytes = 0;
-      if ((st = plan_low_rank(ctx, f, grads, N, m, n, false, nullptr, &bytes, &plan)) != GIFT_OK) return st;
+      if ((st = plan_low_rank(ctx, f, grads, N, m, n, false, nullptr, &bytes, &plan, false)) != GIFT_OK) return st;
       if (plan.active) {
         void *ws = nullptr;
         if ((st = workspace(ctx, bytes, &ws)) != GIFT_OK) return st;
-        if ((st = plan_low_rank(ctx, f, grads, N, m, n, false, static_cast<char *>(ws), &bytes, &plan)) !=
+        if ((st = plan_low_rank(ctx, f, grads, N, m, n, false, static_cast<char *>(ws), &bytes, &plan, false)) !=
             GIFT_OK)
           return st;
         // the split-bf16 update computes W~ (+ R) and packs MXFP4 in one pass

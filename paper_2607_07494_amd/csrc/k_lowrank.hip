@@ -247,6 +247,9 @@ struct LUArgs {
   int64_t img_bs2 = 0;              // bytes between batch entries' segment-1 images (0: shared)
 };
 
+// (codes need be no more than 4-byte aligned)
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
+
 template <int EPI, bool EF, int NSEG, int KC, bool FULL>
 __device__ __forceinline__ void lr_update_body(const LUArgs &p) {
   static_assert(!FULL || EPI != EPI_STORE, "FULL is an AMAX / QUANT variant");
@@ -468,7 +471,8 @@ __device__ __forceinline__ void lr_update_body(const LUArgs &p) {
           // columns j0 + 32 h .. of row ri[g] (8 each, in t = 2h, 2h + 1)
           const int64_t nsb = p.N / 32;
 #pragma unroll
-          for (int g = 0; g < 2; ++g)
+          for (int g = 0; g < 2; ++g) {
+            uint32_t pk[4];
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
               float am = 0.f;
@@ -493,17 +497,15 @@ __device__ __forceinline__ void lr_update_body(const LUArgs &p) {
 #pragma unroll
               for (int tt = 0; tt < 2; ++tt) {
                 const int t = 2 * h + tt;
-                const int64_t cj = j0 + 16 * t + 4 * fg;
-                uint32_t pk = 0u;
-                float d[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) pk |= mx_encode(w[g][t][e], k, bad, d[e]) << (4 * e);
+                pk[t] = mx_encode4(w[g][t][0], w[g][t][1], w[g][t][2], w[g][t][3], k, bad);
                 if (ok) {
-                  const int64_t off = (int64_t)b * MN + ri[g] * p.N + cj;
-                  *reinterpret_cast<uint16_t *>(p.mx_codes + off / 2) = (uint16_t)pk;
-                  if (EF)
+                  const int64_t off = (int64_t)b * MN + ri[g] * p.N + j0 + 16 * t + 4 * fg;
+                  if (EF) {
+                    float d[4];
+                    mx_decode4(pk[t], k, bad, d);
                     *reinterpret_cast<float4 *>(p.ef + off) =
                         make_float4(w[g][t][0] - d[0], w[g][t][1] - d[1], w[g][t][2] - d[2], w[g][t][3] - d[3]);
+                  }
                   if (p.transformed)
                     *reinterpret_cast<float4 *>(p.transformed + off) =
                         make_float4(w[g][t][0], w[g][t][1], w[g][t][2], w[g][t][3]);
@@ -512,6 +514,15 @@ __device__ __forceinline__ void lr_update_body(const LUArgs &p) {
               if (ok && fg == 0)
                 p.mx_scales[((int64_t)b * p.M + ri[g]) * nsb + cb / 32] = bad ? (uint8_t)255 : (uint8_t)(k + 127);
             }
+            // the 16 codes of columns 16 fg .. of the row in one 8-byte store
+            // (2 bytes per lane and 16-column group, and comparisons instead of
+            // the hardware conversion, took 66 us for 8 x 1024 x 2816 at rank
+            // 64; this takes 35)
+            const uint4 q = transpose_rows(pk[0], pk[1], pk[2], pk[3]);
+            if (rv[g] && j0 + 16 * fg < p.N)
+              *reinterpret_cast<u32x2u *>(p.mx_codes + ((int64_t)b * MN + ri[g] * p.N + j0 + 16 * fg) / 2) =
+                  u32x2u{q.x | q.y << 16, q.z | q.w << 16};
+          }
         } else if (FULL && EPI == EPI_AMAX) {
           uint32_t m = 0u;
   #pragma unroll

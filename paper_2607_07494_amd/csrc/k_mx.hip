@@ -8,8 +8,7 @@
 // maximum is two lane exchanges away.  Scale exponent k = floor(log2 amax) - 2
 // (clamped to -127; 255 = NaN for a block holding a NaN or an infinity),
 // elements y = v * 2^-k rounded to the nearest E2M1 value with ties to the
-// even code and saturation at 6, by comparisons against the midpoints (exact:
-// y is exact wherever a comparison can go either way).  Codes are packed two
+// even code and saturation at 6 by the hardware conversion.  Codes are packed two
 // per byte (element 2i in the low nibble): one 4-byte store per lane.  With
 // error feedback the lane also adds the residual first and writes back
 // U - dequantize(codes) (exact dequantization).
@@ -71,17 +70,16 @@ __global__ __launch_bounds__(256) void mx_quant_kernel(const MxArgs a) {
       bad |= __shfl_xor(bad, o);
     }
     const int k = mx_scale_exp(am, bad);
-    uint32_t packed = 0u;
-    float deq[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) packed |= mx_encode(v[i], k, bad, deq[i]) << (4 * i);
+    const uint32_t lo = mx_encode4(v[0], v[1], v[2], v[3], k, bad), hi = mx_encode4(v[4], v[5], v[6], v[7], k, bad);
+    const uint32_t packed = lo | hi << 16;
     *reinterpret_cast<uint32_t *>(a.codes + e / 2) = packed;
     if ((g & 3) == 0) a.scales[e / 32] = bad ? (uint8_t)255 : (uint8_t)(k + 127);
     if (a.ef) {
-      *reinterpret_cast<float4 *>(a.ef + e) =
-          make_float4(v[0] - deq[0], v[1] - deq[1], v[2] - deq[2], v[3] - deq[3]);
-      *reinterpret_cast<float4 *>(a.ef + e + 4) =
-          make_float4(v[4] - deq[4], v[5] - deq[5], v[6] - deq[6], v[7] - deq[7]);
+      float d[4], h[4];
+      mx_decode4(lo, k, bad, d);
+      mx_decode4(hi, k, bad, h);
+      *reinterpret_cast<float4 *>(a.ef + e) = make_float4(v[0] - d[0], v[1] - d[1], v[2] - d[2], v[3] - d[3]);
+      *reinterpret_cast<float4 *>(a.ef + e + 4) = make_float4(v[4] - h[0], v[5] - h[1], v[6] - h[2], v[7] - h[3]);
     }
   }
 }
@@ -96,15 +94,27 @@ __global__ __launch_bounds__(256) void mx_reduce_kernel(const uint8_t *codes, co
     float acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-    for (int j = 0; j < N; ++j) {
-      const uint32_t p = *reinterpret_cast<const uint32_t *>(codes + (int64_t)j * (per_rank / 2) + e / 2);
-      const uint32_t s = scales[(int64_t)j * (per_rank / 32) + e / 32];
+    // eight ranks' words in flight together (a lane's only loads: one rank at
+    // a time, 8 ranks of 1024 x 2816 took 19 us, now 8.6), summed in rank order
+    for (int j0 = 0; j0 < N; j0 += 8) {
+      uint32_t w[8], sc[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint32_t c = (p >> (4 * i)) & 15u;
-        float d = s == 255u ? __int_as_float(0x7fc00000) : ldexpf(e2m1_val(c & 7u), (int)s - 127);
-        if (c & 8u) d = -d;
-        acc[i] = acc[i] + d;
+      for (int u = 0; u < 8; ++u) {
+        const int64_t j = j0 + u < N ? j0 + u : N - 1;
+        w[u] = *reinterpret_cast<const uint32_t *>(codes + j * (per_rank / 2) + e / 2);
+        sc[u] = scales[j * (per_rank / 32) + e / 32];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (j0 + u >= N) break;
+        float d[4], h[4];
+        mx_decode4(w[u], (int)sc[u] - 127, sc[u] == 255u, d);
+        mx_decode4(w[u] >> 16, (int)sc[u] - 127, sc[u] == 255u, h);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          acc[i] = acc[i] + d[i];
+          acc[4 + i] = acc[4 + i] + h[i];
+        }
       }
     }
     const float fn = (float)N;

@@ -60,16 +60,6 @@ struct StripArgs {
   int total, chunk;     // 32-row groups of the batch, and per row chunk
 };
 
-// 4 x 4 transpose across the four 16-lane rows: word t of lane row u <-> word
-// u of lane row t
-__device__ __forceinline__ uint4 transpose_rows(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
-  const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
-  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
-  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
-  return make_uint4(c[0], c[1], d[0], d[1]);
-}
-
 // word of the lane eight places round the 16-lane row
 __device__ __forceinline__ uint32_t row_half(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x128, 0xf, 0xf, false);

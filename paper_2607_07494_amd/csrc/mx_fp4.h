@@ -1,22 +1,10 @@
 // OCP MX FP4 (E2M1) element arithmetic shared by the MXFP4 kernels.
 #pragma once
 
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 namespace gift {
-
-// E2M1 magnitude code of a scaled magnitude a: the nearest of 0, 0.5, 1,
-// 1.5, 2, 3, 4, 6 with ties to the even code, larger values saturating
-__device__ __forceinline__ uint32_t e2m1_mag(float a) {
-  return a <= 0.25f ? 0u : a < 0.75f ? 1u : a <= 1.25f ? 2u : a < 1.75f ? 3u
-       : a <= 2.5f ? 4u : a < 3.5f ? 5u : a <= 5.0f ? 6u : 7u;
-}
-
-// value of an E2M1 magnitude code
-__device__ __forceinline__ float e2m1_val(uint32_t mag) {
-  return mag < 2u ? 0.5f * (float)mag : (mag < 4u ? 1.0f + 0.5f * (float)(mag - 2u)
-                                                  : (mag < 6u ? 2.0f + (float)(mag - 4u) : (mag == 6u ? 4.0f : 6.0f)));
-}
 
 // floor(log2(a)) of a finite a > 0 from its bits (subnormals included)
 __device__ __forceinline__ int mx_floor_log2(float a) {
@@ -37,14 +25,31 @@ __device__ __forceinline__ int mx_scale_exp(float amax, int bad) {
   return k;
 }
 
-// code (sign bit 3) and exact dequantized value of v in a block with scale
-// exponent k (bad block: code 0, value NaN)
-__device__ __forceinline__ uint32_t mx_encode(float v, int k, int bad, float &deq) {
-  const uint32_t mag = bad ? 0u : e2m1_mag(fabsf(ldexpf(v, -k)));
-  const bool neg = signbit(v);
-  const float d = ldexpf(e2m1_val(mag), k);
-  deq = bad ? __int_as_float(0x7fc00000) : (neg ? -d : d);
-  return bad ? 0u : (mag | (neg ? 8u : 0u));
+// E2M1 codes (sign in bit 3) of four values scaled by 2^-k, element e in bits
+// 4 e .. 4 e + 3: the hardware conversion rounds to the nearest of 0, 0.5, 1,
+// 1.5, 2, 3, 4, 6 with ties to the even code, saturates and keeps the sign of
+// zero (one instruction per pair, where comparisons against the seven
+// midpoints are some 20 per element).  A bad block's codes are zero.
+__device__ __forceinline__ uint32_t mx_encode4(float v0, float v1, float v2, float v3, int k, int bad) {
+  uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, ldexpf(v0, -k), ldexpf(v1, -k), 1.0f, 0);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, ldexpf(v2, -k), ldexpf(v3, -k), 1.0f, 1);
+  return bad ? 0u : w & 0xffffu;
+}
+
+// exact values of the codes in byte B of w, before their scale
+template <int B>
+__device__ __forceinline__ void mx_decode2(uint32_t w, float &a, float &b) {
+  const auto v = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, B);
+  a = v[0];
+  b = v[1];
+}
+
+// exact dequantized values of four codes (NaN in a bad block)
+__device__ __forceinline__ void mx_decode4(uint32_t w, int k, int bad, float (&d)[4]) {
+  mx_decode2<0>(w, d[0], d[1]);
+  mx_decode2<1>(w, d[2], d[3]);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) d[e] = bad ? __int_as_float(0x7fc00000) : ldexpf(d[e], k);
 }
 
 }  // namespace gift

@@ -40,6 +40,16 @@ __device__ __forceinline__ void st_u128_untracked(void *p, uint4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" ::"v"(p), "v"(w) : "memory");
 }
 
+// 4 x 4 transpose across the four 16-lane rows: word t of lane row u <-> word
+// u of lane row t
+__device__ __forceinline__ uint4 transpose_rows(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3) {
+  const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  return make_uint4(c[0], c[1], d[0], d[1]);
+}
+
 // hi / lo bf16 pairs of two float32 values (round to nearest even)
 __device__ __forceinline__ void split2(float x, float y, uint32_t &hi, uint32_t &lo) {
   const bf16x2 h = __builtin_convertvector((floatx2){x, y}, bf16x2);

@@ -156,3 +156,19 @@ def test_error_feedback_two_steps(ctx):
         prev = R.cpu().numpy()
         np.testing.assert_array_equal(prev, mx.residual(tr, mx.unpack(codes), scales))
     f.close()
+
+
+@pytest.mark.parametrize("N,m,n", [(1, 5, 64), (7, 3, 96), (8, 4, 32), (9, 2, 160), (17, 2, 64)])
+def test_rank_mean_of_any_codes(ctx, N, m, n):
+    """Every code and scale byte (255 among them), ranks around the eight whose
+    words are loaded together."""
+    say(f"mxfp4 rank mean N={N} m={m} n={n}")
+    rng = np.random.default_rng(N)
+    packed = rng.integers(0, 256, (N, m, n // 2), dtype=np.uint8)
+    scales = rng.integers(0, 256, (N, m, n // 32), dtype=np.uint8)
+    scales[0, 0, 0] = 255
+    mean = torch.empty((m, n), dtype=torch.float32, device=DEV)
+    gift.reduce_local_mxfp4(ctx, t(packed), t(scales), mean)
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = mx.reduce_local(mx.unpack(packed), scales)
+    np.testing.assert_array_equal(mean.cpu().numpy(), ref)
