@@ -356,6 +356,14 @@ struct SideJob {
 // d_xtab), otherwise the float32 tile kernel (host pointers h_x; bf16 inputs
 // are widened into Xc [T, dim] first).
 bool statistics_direct(gift_dtype dtype, int64_t dim);
+// k_syrk.hip: the bf16 statistics of several dimensions in one launch
+struct SyrkJob {
+  const uint16_t *const *x_table;   // device table of the members' inputs
+  int members;
+  int64_t dim;
+  float *A;                         // [members, dim, dim]
+};
+gift_status launch_syrk_bf16(gift_ctx *ctx, const SyrkJob *jobs, int count, int64_t T, float scale);
 gift_status launch_statistics(gift_ctx *ctx, const void *const *d_xtab, const void *const *h_x, int G,
                               int64_t T, int64_t dim, gift_dtype dtype, float *A, float *Xc);
 gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs, int64_t T,

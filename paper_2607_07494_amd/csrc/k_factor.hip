@@ -54,9 +54,6 @@
 
 namespace gift {
 
-gift_status launch_syrk_bf16(gift_ctx *ctx, const uint16_t *const *x_table, int members,
-                             int64_t T, int64_t dim, float scale, float *A);
-
 namespace {
 
 constexpr int kSmallThreads = 1024;
@@ -730,8 +727,10 @@ gift_status launch_statistics(gift_ctx *ctx, const void *const *d_xtab, const vo
                               int64_t T, int64_t dim, gift_dtype dtype, float *A, float *Xc) {
   const float inv_T = (float)(1.0 / (double)T);
   gift_status st;
-  if (statistics_direct(dtype, dim))
-    return launch_syrk_bf16(ctx, reinterpret_cast<const uint16_t *const *>(d_xtab), G, T, dim, inv_T, A);
+  if (statistics_direct(dtype, dim)) {
+    const SyrkJob j{reinterpret_cast<const uint16_t *const *>(d_xtab), G, dim, A};
+    return launch_syrk_bf16(ctx, &j, 1, T, inv_T);
+  }
   for (int m = 0; m < G; ++m) {
     const float *X32 = static_cast<const float *>(h_x[m]);
     if (dtype == GIFT_BF16) {
@@ -916,8 +915,16 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
     for (Group &g : groups) g.xtab = d_xt + g.first;
   }
 
-  // 1. statistics A_g = X_g^T X_g / T
+  // 1. statistics A_g = X_g^T X_g / T (bf16 inputs of every dimension together)
+  std::vector<SyrkJob> direct;
+  for (const Group &g : groups)
+    if (g.bf16_direct) direct.push_back(SyrkJob{reinterpret_cast<const uint16_t *const *>(g.xtab), g.G, g.dim, g.Amat});
+  // (largest dimension first: its tiles read the longest rows)
+  std::stable_sort(direct.begin(), direct.end(), [](const SyrkJob &x, const SyrkJob &y) { return x.dim > y.dim; });
+  if (!direct.empty() && (st = launch_syrk_bf16(ctx, direct.data(), (int)direct.size(), T, (float)(1.0 / (double)T))) != GIFT_OK)
+    return st;
   for (Group &g : groups) {
+    if (g.bf16_direct) continue;
     std::vector<const void *> xs;
     for (const SideJob &j : g.jobs) xs.push_back(j.x);
     if ((st = launch_statistics(ctx, g.xtab, xs.data(), g.G, T, g.dim, dtype, g.Amat, g.Xc)) != GIFT_OK)

@@ -96,6 +96,28 @@ def test_statistics_repeat_is_deterministic(ctx):
     assert torch.equal(A1, A2)
 
 
+def test_refresh_of_many_dimensions(ctx):
+    """Ten input dimensions in one refresh, more than one launch of the bf16
+    statistics takes, a dimension outside that kernel among them: the tiles are
+    those of a refresh alone, so the factors are too."""
+    say("statistics of many dimensions")
+    T, r = 96, 4
+    dims = [8, 264, 16, 300, 24, 256, 40, 520, 72, 104]
+    acts = [device_input(T, d, "bf16" if d != 300 else "f32", seed=7200 + d)[1].to(torch.bfloat16) for d in dims]
+    batch = [gift.Factor(ctx, 8, d, r, gift.SIDE_INPUT, seed=d) for d in dims]
+    gift.factor_update_batch(ctx, batch, acts, [None] * len(dims), iters=2)
+    for d, x, f in zip(dims, acts, batch):
+        one = gift.Factor(ctx, 8, d, r, gift.SIDE_INPUT, seed=d)
+        one.update(acts=x, iters=2)
+        for a, b in zip(f.export(gift.SIDE_INPUT), one.export(gift.SIDE_INPUT)):
+            if isinstance(a, torch.Tensor):
+                assert torch.equal(a, b), d
+            else:
+                assert a == b, d
+        one.close()
+        f.close()
+
+
 def test_statistics_argument_errors(ctx):
     say("statistics errors")
     x = torch.zeros((16, 8), dtype=torch.bfloat16, device=DEV)
