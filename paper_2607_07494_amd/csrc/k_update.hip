@@ -939,6 +939,15 @@ bool update_kernel_eligible(const TileJob &j) {
     if (g.a.ld % 4 || g.b.ld % 4 || g.a.bs % 4 || g.b.bs % 4) return false;
     if (!al16(g.a.ptr) || !al16(g.b.ptr)) return false;
   }
+  // Odd rows, odd addresses and ranks 48 and 96 come here for their maxima and
+  // codes where a wave's 16 x 64 tile lies in one scale block; over other
+  // blocks the per-element maxima cost more than the tile kernel's products
+  // (16 x 2900 x 2001, both sides at rank 64, 100-column blocks: 10.8 ms here,
+  // 2.05 there).  (The rule sees what both passes share.)
+  if (j.amax != nullptr && (j.N % 4 != 0 || K == 48 || K == 96 || !al16(j.D) || (j.ef && !al16(j.ef)))) {
+    const int64_t br = j.geom.br > 0 ? j.geom.br : j.M, bc = j.geom.bc > 0 ? j.geom.bc : j.N;
+    if (!((br % 16 == 0 || br >= j.M) && (bc % 64 == 0 || bc >= j.N))) return false;
+  }
   // (W, the residual, W~, the output and the codes at any address)
   if (!j.D && !j.d_tab) return false;
   if (j.amax == nullptr) {  // decode store: dense output, D dense
