@@ -939,6 +939,9 @@ bool update_kernel_eligible(const TileJob &j) {
     if (g.a.ld % 4 || g.b.ld % 4 || g.a.bs % 4 || g.b.bs % 4) return false;
     if (!al16(g.a.ptr) || !al16(g.b.ptr)) return false;
   }
+  // (two-sided stores at rank 96, 192 steps per tile: 1400 x 4000 75 us here,
+  // 62 on the tile kernel)
+  if (j.amax == nullptr && j.nseg == 2 && K == 96 && j.N % 4 == 0) return false;
   // Odd rows, odd addresses and ranks 48 and 96 come here for their maxima and
   // codes where a wave's 16 x 64 tile lies in one scale block; over other
   // blocks the per-element maxima cost more than the tile kernel's products
