@@ -198,7 +198,9 @@ void gift_factor_destroy(gift_factor *f);
  * Rayleigh-Ritz extraction, sigma^2 = mean of the remaining eigenvalues
  * (floored at damping * tr/dim), and the coefficients
  *   c_i = sqrt(sigma^2/lambda_i) - 1,  c'_i = sqrt(lambda_i/sigma^2) - 1,
- * so that S^-1 = I + U diag(c) U^T and S = I + U diag(c') U^T. */
+ * so that S^-1 = I + U diag(c) U^T and S = I + U diag(c') U^T.  Statistics
+ * without a positive trace (all zero, or not finite) give the identity (U, c,
+ * c' and sigma^2 zero); the next update goes on from the subspace there was. */
 gift_status gift_factor_update(gift_ctx *ctx, gift_factor *f, const void *acts,
                                const void *out_grads, int64_t T, gift_dtype dtype,
                                int32_t iters);

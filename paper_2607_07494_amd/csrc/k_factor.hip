@@ -67,7 +67,7 @@ struct Member {
   const float *A;        // statistics [dim, dim]
   float *start;          // start block [k, dim] (rows = basis vectors)
   const float *rot;      // rotated Ritz basis V^T Q [k, dim]
-  const float *theta;    // Ritz values [k], descending
+  float *theta;          // Ritz values [k], descending; theta[0] = 0 marks an identity (finalize_coef_kernel)
   int64_t dim;
   int k, r;
   uint32_t seed_lo, seed_hi;
@@ -115,6 +115,18 @@ __global__ void gather_start_kernel(const Member *mem) {
     }
     M.start[t] = v;
   }
+}
+
+// The orthonormal start block of a member without a basis of its own becomes
+// its basis, so that a refresh whose statistics give the identity (below)
+// leaves the next one an orthonormal start.
+__global__ void keep_start_kernel(const Member *mem) {
+  const Member M = mem[blockIdx.y];
+  if (M.mode == 1) return;
+  const int64_t total = (int64_t)M.k * M.dim;
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
+       t += (int64_t)gridDim.x * blockDim.x)
+    M.Qt[t] = M.start[t];
 }
 
 __global__ void bf16_to_f32_kernel(float *dst, const uint16_t *src, int64_t n) {
@@ -545,7 +557,11 @@ __global__ __launch_bounds__(kSmallThreads) void rr_eig_global_kernel(const Smal
   rr_emit(W, norms, perm, k, J.out, J.theta);
 }
 
-// sigma^2 and the coefficients of every member (one workgroup each)
+// sigma^2 and the coefficients of every member (one workgroup each).
+// Statistics without a positive trace, or whose largest Ritz value is not
+// positive (not finite, or lost below float32's range), give the identity:
+// their basis is not orthonormal and may hold NaN (Y = Q A = 0 has no R^-1 in
+// float32), so none of it is kept.
 __global__ __launch_bounds__(256) void finalize_coef_kernel(const Member *mem) {
   __shared__ double red[2][4];
   const Member M = mem[blockIdx.x];
@@ -564,7 +580,9 @@ __global__ __launch_bounds__(256) void finalize_coef_kernel(const Member *mem) {
   __syncthreads();
   tr = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
   top = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-  const bool identity = !(tr > 0.0) || M.r == 0;
+  const bool identity = !(tr > 0.0) || M.r == 0 || !(M.theta[0] > 0.f);
+  __syncthreads();
+  if (identity && tid == 0 && M.k > 0) M.theta[0] = 0.f;
   const double floor = (double)M.damping * tr / (double)M.dim;
   double sigma2 = 0.0;
   if (!identity) {
@@ -576,7 +594,7 @@ __global__ __launch_bounds__(256) void finalize_coef_kernel(const Member *mem) {
     }
   }
   for (int i = tid; i < M.r; i += 256) {
-    double l = M.theta[i] > 0.f ? (double)M.theta[i] : 0.0;
+    double l = !identity && M.theta[i] > 0.f ? (double)M.theta[i] : 0.0;
     double cf = 0.0, ci = 0.0;
     if (!identity) {
       const double fl = M.r >= M.dim ? floor : sigma2;
@@ -593,12 +611,18 @@ __global__ __launch_bounds__(256) void finalize_coef_kernel(const Member *mem) {
 
 // Layouts of every member from its rotated basis (grid.y = member): Qt (all k
 // rows, the warm start), Ut (first r rows), and U, U diag(c_fwd),
-// U diag(c_inv) as [dim, r] through an LDS transpose of 32-row tiles.
+// U diag(c_inv) as [dim, r] through an LDS transpose of 32-row tiles.  An
+// identity member's are zero, and its Qt stays the basis it had.
 constexpr int kTileRows = 32;
 __global__ __launch_bounds__(256) void finalize_layout_kernel(const Member *mem) {
   __shared__ float tile[kLayoutRows][kTileRows + 1];
   const Member M = mem[blockIdx.y];
   const int tid = threadIdx.x;
+  if (!(M.theta[0] > 0.f)) {
+    for (int64_t t = (int64_t)blockIdx.x * 256 + tid; t < M.dim * M.r; t += (int64_t)gridDim.x * 256)
+      M.U[t] = M.Ut[t] = M.Uc[t] = M.Uci[t] = 0.f;
+    return;
+  }
   const int64_t ntiles = (M.dim + kTileRows - 1) / kTileRows;
   for (int64_t tb = blockIdx.x; tb < ntiles; tb += gridDim.x) {
     const int64_t i0 = tb * kTileRows;
@@ -1049,6 +1073,11 @@ gift_status factor_refresh_batch(gift_ctx *ctx, const std::vector<SideJob> &jobs
   if (any_cold) {
     GIFT_HIP_TRY(hipMemcpyAsync(Y_all, Qw_all, sizeof(float) * qy_floats, hipMemcpyDeviceToDevice, stream));
     if ((st = cholqr2()) != GIFT_OK) return st;
+    {
+      ProfileScope prof(ctx, GIFT_KERNEL_FACTOR);
+      hipLaunchKernelGGL(keep_start_kernel, dim3(grid_for(max_kd, 256, 2048), total), dim3(256), 0, stream, d_mem);
+    }
+    if ((st = check_launch("keep_start_kernel")) != GIFT_OK) return st;
   }
   for (int it = 0; it < iters; ++it) {
     for (const Group &g : groups)

@@ -86,3 +86,55 @@ def test_eigensolver_degenerate_spectra(ctx):  # noqa: F811
     got = exported(f, gift.SIDE_INPUT)
     assert np.all(got.c_fwd == 0) and np.all(got.c_inv == 0) and got.sigma2 == 0.0
     f.close()
+
+
+def same_factor(a, b):
+    for x, y in zip(a.export(gift.SIDE_INPUT), b.export(gift.SIDE_INPUT)):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("dim,r,iters", [(96, 16, 2), (96, 16, 0), (160, 33, 2), (320, 80, 1), (300, 129, 1)])
+@pytest.mark.parametrize("bad", [0.0, float("nan")])
+def test_statistics_without_a_trace(ctx, dim, r, iters, bad):  # noqa: F811
+    """A refresh on all-zero (or not finite) statistics, first and after
+    another one, for every solver range: the identity in every layout, and the
+    next refresh goes on from the basis there was (k = 32, 66, 160, 258)."""
+    say(f"no trace dim={dim} r={r} iters={iters} bad={bad}")
+    X, _ = factor_inputs(700 + dim, 2 * dim, dim)
+    X2, _ = factor_inputs(701 + dim, 2 * dim, dim)
+    none = torch.full((2 * dim, dim), bad, device="cuda")
+    m, N = 24, 2
+    g = torch.randn((N, m, dim), device="cuda")
+
+    def codes_of(f):
+        codes = torch.empty((N, m, dim), dtype=torch.uint8, device="cuda")
+        scales = torch.empty((N, 1, 1), device="cuda")
+        gift.encode(ctx, f, g, codes, scales)
+        mean, out = torch.empty((m, dim), device="cuda"), torch.empty((m, dim), device="cuda")
+        gift.reduce_local(ctx, codes, scales, mean)
+        gift.decode(ctx, f, mean, out)
+        return codes, scales, mean, out
+
+    def check_identity(f):
+        U, cf, ci, s2 = f.export(gift.SIDE_INPUT)
+        for v in (U, cf, ci, s2):
+            assert torch.all(v == 0)
+        got, want = codes_of(f), codes_of(None)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        assert torch.equal(got[3], got[2])
+
+    f, fresh = (gift.Factor(ctx, m, dim, r, gift.SIDE_INPUT, seed=dim) for _ in range(2))
+    f.update(acts=none, iters=iters)
+    check_identity(f)
+    # beside a member with statistics, in one call
+    gift.factor_update_batch(ctx, [f, fresh], [none, t(X)], [None, None], iters=iters)
+    check_identity(f)
+    f.update(acts=t(X), iters=iters)
+    same_factor(f, fresh)
+    f.update(acts=none, iters=iters)
+    check_identity(f)
+    for x in (f, fresh):
+        x.update(acts=t(X2), iters=iters)
+    same_factor(f, fresh)
+    f.close()
+    fresh.close()
