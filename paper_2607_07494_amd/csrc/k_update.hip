@@ -689,7 +689,12 @@ __global__ __launch_bounds__(kThreads) void proj_kernel(const PArgs p) {
 // blocks of 16 NT columns, for the refresh's Q A at k > 128 (k = 256, six
 // factors of 4096: 1047 us on proj_kernel, whose waves read Q from L2 for 16
 // rows each, 617 here).
-template <int NT, bool RAG, int RG>
+// FOLD: the contraction in four float32 chains, summed in order, as
+// proj_kernel's four waves form it: over a dimension of 4096 one chain is off
+// by 5e-7 of Q A, four by 1.5e-7, and the iteration hands it on to the factor.
+// (A second set of accumulators: blocks of at most 64 columns keep two waves
+// per SIMD with two strips, and cost what 128-column ones do without it.)
+template <int NT, bool RAG, int RG, bool FOLD>
 __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, int parts, int blocks) {
   constexpr int C = 16 * NT;
   constexpr int KC = 64;                // contraction steps per chunk
@@ -756,6 +761,15 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
   for (int g = 0; g < RG; ++g)
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[g][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+  floatx4 sum[FOLD ? RG : 1][FOLD ? NT : 1];   // the finished chains (-0 + x = x)
+  if (FOLD) {
+#pragma unroll
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) sum[g][t] = floatx4{-0.f, -0.f, -0.f, -0.f};
+  }
+  const int per = FOLD ? (int)(((p.K + 15) / 16 + 3) / 4) : 0;   // 16-step groups of a chain
+  int left = per;
   if (nchunks > 0) {
     load_y(k0);
     load_x(k0);
@@ -789,9 +803,25 @@ __global__ __launch_bounds__(kThreads) void proj_staged_kernel(const PArgs p, in
       GIFT_STEP(z);
       GIFT_STEP(w);
 #undef GIFT_STEP
+      if (FOLD && --left == 0) {   // (wave-uniform)
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            sum[g][t] += acc[g][t];
+            acc[g][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+        left = per;
+      }
     }
     if (more) store_y(buf ^ 1);
     __syncthreads();
+  }
+  if (FOLD) {
+#pragma unroll
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[g][t] += sum[g][t];
   }
   // lane holds part z of out[ri][c0 + 16t + 4fg + v]
 #pragma unroll
@@ -1127,26 +1157,42 @@ gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
   a.out_t = tr ? 1 : 0;
   a.tab = j.decode_tab;
   ProfileScope prof(ctx, j.kernel_family);
-  // (the transposed form, the refresh's Q A at k > 128, in blocks of equal width)
-  const bool staged_t = tr && j.ksplit <= 1 && staged_aligned(j) && a.C > 128 && a.C % 16 == 0 &&
-                        (a.C / 16) % ((a.C + 127) / 128) == 0;
+  const int64_t strips = (a.M + 15) / 16 * j.batch;
+  // The transposed form, the refresh's Q A at k > 128, in blocks of equal
+  // width.  Its chains are those of proj_kernel below: four where that splits
+  // the contraction over waves (FOLD), else one.  Width of a FOLD block: 3, 4,
+  // 5 or 7 tiles, the first that divides (6 x 4096 at k = 192: blocks of 3 / 4
+  // tiles 1.91 / 2.20 ms of products per refresh, 12 x 1536 0.96 / 0.89; k =
+  // 160: 5 / 2 tiles 1.67 / 1.82; k = 224: 7 / 2 tiles 2.36 / 2.61).
+  const int ct = a.C / 16;
+  const bool tr_ok = tr && j.ksplit <= 1 && staged_aligned(j) && a.C > 128 && a.C % 16 == 0;
+  const int fold = !tr_ok || strips >= 4096 ? 0 : ct % 3 == 0 ? 3 : ct % 4 == 0 ? 4 : ct % 5 == 0 ? 5 : ct % 7 == 0 ? 7 : 0;
+  const bool staged_t = fold || (tr_ok && strips >= 4096 && ct % ((a.C + 127) / 128) == 0);
   if (staged_eligible(j) || staged_t) {
     const int parts = j.ksplit > 1 ? j.ksplit : 1;
-    const int blocks = staged_t ? (a.C + 127) / 128 : 1;
-    const int nt = a.C / 16 / blocks;
+    const int blocks = fold ? ct / fold : staged_t ? (a.C + 127) / 128 : 1;
+    const int nt = ct / blocks;
     const bool rag = !staged_aligned(j);
     // 128-row workgroups once they fill the chip's slots (two per CU)
-    const bool two = !rag && (a.M + 127) / 128 * parts * blocks * j.batch >= 512;
+    const bool two = !rag && fold <= 4 && (a.M + 127) / 128 * parts * blocks * j.batch >= 512;
     const int rows = two ? 128 : 64;
     const dim3 sgrid((unsigned)((a.M + rows - 1) / rows), (unsigned)(parts * blocks), (unsigned)j.batch);
-#define GIFT_PROJS(NT)                                                                                             \
-  do {                                                                                                             \
-    if (rag)                                                                                                       \
-      hipLaunchKernelGGL((proj_staged_kernel<NT, true, 1>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks); \
-    else if (two)                                                                                                  \
-      hipLaunchKernelGGL((proj_staged_kernel<NT, false, 2>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks); \
-    else                                                                                                           \
-      hipLaunchKernelGGL((proj_staged_kernel<NT, false, 1>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks); \
+#define GIFT_STAGED(NT, RAG, RG, FOLD) \
+  hipLaunchKernelGGL((proj_staged_kernel<NT, RAG, RG, FOLD>), sgrid, dim3(kThreads), 0, ctx->stream, a, parts, blocks)
+    if (fold) {
+      if (nt == 3 && two) GIFT_STAGED(3, false, 2, true);
+      else if (nt == 3) GIFT_STAGED(3, false, 1, true);
+      else if (nt == 4 && two) GIFT_STAGED(4, false, 2, true);
+      else if (nt == 4) GIFT_STAGED(4, false, 1, true);
+      else if (nt == 5) GIFT_STAGED(5, false, 1, true);
+      else GIFT_STAGED(7, false, 1, true);
+      return check_launch("proj_staged_kernel");
+    }
+#define GIFT_PROJS(NT)                             \
+  do {                                             \
+    if (rag) GIFT_STAGED(NT, true, 1, false);      \
+    else if (two) GIFT_STAGED(NT, false, 2, false); \
+    else GIFT_STAGED(NT, false, 1, false);         \
   } while (0)
     switch (nt) {
       case 1: GIFT_PROJS(1); break;
@@ -1159,10 +1205,10 @@ gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
       default: GIFT_PROJS(8); break;
     }
 #undef GIFT_PROJS
+#undef GIFT_STAGED
     return check_launch("proj_staged_kernel");
   }
   // split K over the waves of a workgroup when strips alone would not fill the GPU
-  const int64_t strips = (a.M + 15) / 16 * j.batch;
   const int ks = strips >= 4096 ? 1 : (strips >= 2048 ? 2 : 4);
   const int nt = a.C <= 16 ? 1 : (a.C <= 32 ? 2 : 4);
   const int rows_per_wg = 16 * (4 / ks);

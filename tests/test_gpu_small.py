@@ -138,3 +138,31 @@ def test_statistics_without_a_trace(ctx, dim, r, iters, bad):  # noqa: F811
     same_factor(f, fresh)
     f.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("dim,r", [(4096, 128), (4096, 72), (4092, 80), (2052, 112), (4096, 120), (4096, 48)])
+def test_product_chains(ctx, dim, r):  # noqa: F811
+    """Q A at k > 128 sums its contraction in four chains, not one.  1024 tokens
+    of 1, 2 and 3 give exact statistics, all positive, with one dominant
+    eigenvector, each entry of which then carries the rounding of its own sum
+    of `dim` terms of one sign.  n roundings of a partial sum that grows evenly
+    to S leave S u sqrt(n / 3) / sqrt(3) (u = 2^-24, a rounding's error
+    uniform); the matrix core rounds once per product, or less often.  Measured:
+    one chain 8.3e-7 at 4092, four 2.2e-7, the bound 0.6 of one chain's
+    estimate at a rounding per four products.  (k = 96 runs split-bf16
+    products: 2^-16 each, of random sign.)"""
+    say(f"product chains dim={dim} r={r}")
+    rng = np.random.default_rng(dim + r)
+    X = rng.integers(1, 4, (1024, dim)).astype(np.float64)
+    f = gift.Factor(ctx, 16, dim, r, gift.SIDE_INPUT, seed=1)
+    f.update(acts=t(X.astype(np.float32)), iters=3)
+    u = exported(f, gift.SIDE_INPUT).U[:, 0]
+    v = np.ones(dim)
+    for _ in range(40):
+        v = X.T @ (X @ v)
+        v /= np.linalg.norm(v)
+    err = np.linalg.norm(u * np.sign(u.sum()) / np.linalg.norm(u) - v)
+    one = 2.0 ** -24 * np.sqrt(dim / 4 / 3) / np.sqrt(3)
+    say(f"  error {err:.3g}, one chain {one:.3g}")
+    assert err <= (0.6 * one if r > 64 else 2.0 ** -16 / np.sqrt(3 * dim) * 4 + one)
+    f.close()
