@@ -103,16 +103,13 @@ def parse():
                     help="hardware queues of this process (GPU_MAX_HW_QUEUES, set before the HIP "
                          "runtime starts; 0 keeps the environment's value; default 8 for the "
                          "Llama-600M set, 4 (HIP's own) otherwise). Measured on the Llama-600M "
-                         "set (codec-only step): 4 queues, 4 streams dealt in turn 37.1-38.1 ms "
-                         "(the best with 4 queues; 2, 3, 6 streams and the balanced assignment "
-                         "slower); 8 queues, 6 streams balanced 33.1-34.2 ms over seven runs on "
-                         "three boxes (against 37.9-38.1 for the former on the same box), 5 / 7 / 8 "
-                         "streams 51.1 / 42.5 / 35.3-36.6 ms, 6 streams in turn 48.2 ms; 16 queues, "
-                         "6 / 8 / 12 streams balanced 33.2 / 33.8-34.9 / 50.8 ms. The Llama-300M "
-                         "set keeps 4 streams in turn: 13.0 ms per step, 16.9 with 6 balanced on "
-                         "8 queues. With error feedback (Llama-600M) 8 balanced streams on 8 "
-                         "queues: 44.2-46.7 ms per codec step, 6: 55.0-55.3, 4 in turn on 4 "
-                         "queues: 52.5")
+                         "set (codec-only step): 8 queues, balanced, 1 / 2 / 3 / 4 / 5 / 6 / 7 / 8 / "
+                         "10 streams 46.3 / 44.4 / 42.4 / 42.2 / 42.9 / 43.6 / 43.0 / 42.8 / 44.6 "
+                         "ms; 6 streams on 4 / 16 queues 42.6 / 43.3 ms, 4 streams dealt in turn on "
+                         "4 queues 42.4 ms. With error feedback 4 / 6 / 8 balanced streams 63.7 / "
+                         "63.3 / 62.9 ms; both sides 81.5 / 82.7 / 81.5 ms. The Llama-300M set "
+                         "keeps 4 streams in turn on 4 queues: 13.0 ms per step (2 / 6 / 8 streams "
+                         "13.9 / 13.2 / 13.2, 6 balanced on 8 queues 17.4)")
     ap.add_argument("--breakdown-steps", type=int, default=2,
                     help="untimed steps with every kernel family bracketed by events")
     ap.add_argument("--format", choices=["fp8", "mxfp4"], default="fp8",
@@ -665,6 +662,30 @@ def fidelity_study(args):
     print(json.dumps({"fidelity": rows, "layer": [m, n], "tokens": T}), flush=True)
 
 
+def join(main, streams, event):
+    """`main` waits for everything the other streams hold; event() makes an event."""
+    for st in streams:
+        if st is not main:
+            ev = event()
+            ev.record(st)
+            main.wait_event(ev)
+
+
+def start_together(main, streams, event):
+    """Hold every other stream until what `main` holds by now is done.
+
+    A step begins with this after a join: without it only `main` would wait
+    for the step before, the other streams would run ahead through the
+    following steps, and the intervals between `main`'s events would be no
+    step's time (six streams: 61 ms for the first half of the steps and 33 ms
+    for the rest, of a true 45 ms each, whose median depends on the step count)."""
+    ev = event()
+    ev.record(main)
+    for st in streams:
+        if st is not main:
+            st.wait_event(ev)
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -760,22 +781,18 @@ def main():
                 order.append(a.pop(0))
 
     def join_into_main():
-        for st in streams[1:]:
-            ev = torch.cuda.Event()
-            ev.record(st)
-            main.wait_event(ev)
+        join(main, streams, torch.cuda.Event)
 
     def step(iters, serial=False, refresh=True, codec=True):
         """One step; refresh=False reuses the factors of the last refresh
         (the cadence's other steps), codec=False runs the refresh alone."""
-        join_into_main()           # the refresh rewrites factors the last step's encodes read
-        joined = torch.cuda.Event()
-        joined.record(main)
+        # a step starts when the last one is done on every stream (its averaged
+        # gradients make the weights that the next gradients come from)
+        join_into_main()
+        start_together(main, streams, torch.cuda.Event)
         ready = {}
         for k in (gorder if refresh else ()):
             sid = 0 if serial else gsid[k]
-            if sid != 0:
-                streams[sid].wait_event(joined)
             g = groups[k]
             gift.factor_update_batch(ctxs[sid], [jb.factor for jb in g], [jb.acts for jb in g],
                                      [jb.dgrads for jb in g], iters=iters)

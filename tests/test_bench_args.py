@@ -1,5 +1,6 @@
-"""Host-side checks of bench.py's command line: the schedule each workload
-gets by default, and explicit flags taking precedence (no GPU, no torch)."""
+"""Host-side checks of bench.py: the schedule each workload gets by default,
+explicit flags taking precedence, and step boundaries over several streams (no
+GPU, no torch)."""
 
 import os
 import sys
@@ -45,3 +46,38 @@ def test_more_than_one_gpu_is_refused(capsys, monkeypatch):
     assert e.value.code == 2
     assert "one GPU" in capsys.readouterr().err
     assert "GPU_MAX_HW_QUEUES" not in os.environ   # refused before touching it
+
+
+class Stream:
+    """A queue in virtual time: work runs after what it waits for."""
+
+    def __init__(self):
+        self.now = 0.0
+
+    def run(self, duration):
+        self.now += duration
+
+    def wait_event(self, ev):
+        self.now = max(self.now, ev.at)
+
+
+class Event:
+    def record(self, stream):
+        self.at = stream.now
+
+
+@pytest.mark.parametrize("durations", [(1.0, 3.0), (3.0, 1.0, 2.0), (2.0,)])
+def test_steps_begin_on_every_stream(durations):
+    """Each step takes as long as its slowest stream, whichever that is in that
+    step, and its interval on the main stream says so."""
+    streams = [Stream() for _ in durations]
+    main = streams[0]
+    for step in range(4):
+        bench.join(main, streams, Event)
+        begin = main.now
+        bench.start_together(main, streams, Event)
+        assert all(st.now == begin for st in streams)
+        for i, st in enumerate(streams):
+            st.run(durations[(i + step) % len(durations)])
+        bench.join(main, streams, Event)
+        assert main.now - begin == max(durations)
