@@ -166,3 +166,30 @@ def test_product_chains(ctx, dim, r):  # noqa: F811
     say(f"  error {err:.3g}, one chain {one:.3g}")
     assert err <= (0.6 * one if r > 64 else 2.0 ** -16 / np.sqrt(3 * dim) * 4 + one)
     f.close()
+
+
+@pytest.mark.parametrize("dim,r,count,chains", [(4092, 128, 4, 4), (4092, 96, 4, 4), (4096, 128, 16, 1)])
+def test_product_of_several_factors(ctx, dim, r, count, chains):  # noqa: F811
+    """Q A at k > 128 in workgroups of two strips per wave: each factor's
+    leading eigenvector as in test_product_chains (the statistics of factor i
+    are those of factor 0 with its features moved i places), and a batch of
+    4096 16-row strips, whose sums are one chain (its own estimate for a
+    rounding per product)."""
+    say(f"product of {count} factors dim={dim} r={r}")
+    rng = np.random.default_rng(dim + r)
+    X = rng.integers(1, 4, (1024, dim)).astype(np.float64)
+    v = np.ones(dim)
+    for _ in range(40):
+        v = X.T @ (X @ v)
+        v /= np.linalg.norm(v)
+    fs = [gift.Factor(ctx, 16, dim, r, gift.SIDE_INPUT, seed=1 + i) for i in range(count)]
+    x = t(X.astype(np.float32))
+    gift.factor_update_batch(ctx, fs, [torch.roll(x, 37 * i, 1).contiguous() for i in range(count)],
+                             [None] * count, iters=3)
+    one = 2.0 ** -24 * np.sqrt(dim / 4 / 3) / np.sqrt(3)
+    for i, f in enumerate(fs):
+        u = exported(f, gift.SIDE_INPUT).U[:, 0]
+        err = np.linalg.norm(u * np.sign(u.sum()) / np.linalg.norm(u) - np.roll(v, 37 * i))
+        say(f"  factor {i}: error {err:.3g}, one chain {one:.3g}")
+        assert err <= (0.6 * one if chains == 4 else 2 * one)
+        f.close()
