@@ -991,6 +991,32 @@ bool update_kernel_eligible(const TileJob &j) {
   return true;
 }
 
+// Tiles per workgroup of update_store_kernel, or 0 where update_kernel is the
+// faster one.  A workgroup of 128 rows x `units` tiles, two per CU: the larger
+// it is, the more of a nearly empty last round (or of a short last unit) the
+// chip waits for.  `idle` is the time the rounds take over the time of the work
+// itself; update_kernel's workgroups are a quarter of the size or less and
+// lose little to it.  Measured over 45 grids at ranks 64 and 128, this kernel /
+// update_kernel, us:
+//   idle 1.00: 8 x 1024 x 1024 28.1 / 31.6 and 42.5 / 48.0; 2 x 8192 x 1536 69.9 / 69.2 and 114 / 125
+//   idle 1.09: 8 x 1024 x 2816 91.7 / 86.5 and 157 / 170 (two tiles)
+//   idle 1.19: 24 x 1061 x 1500 124 / 128 and 186 / 219 (four tiles)
+//   idle 1.42: 2 x 2048 x 2820 58.3 / 47.9 and 97.9 / 89.2 (two tiles, two rounds); 3 x 2048 x 2820 76.4 /
+//              69.3 and 128 / 139 (three rounds); 6 x 2048 x 2820 126 / 131 and 197 / 254 (four tiles)
+//   idle 1.94: 3 x 1024 x 2816 49.3 / 40.7 and 81.9 / 75.3
+// (at rank 64 update_kernel holds twice the workgroups per CU and two tiles
+// save it less)
+int store_units(int64_t M, int64_t N, int32_t batch, int K) {
+  const int64_t rows = (M + 127) / 128 * batch, tiles = (N + 63) / 64;
+  int units = 8;
+  while (units > 2 && rows * ((tiles + units - 1) / units) < 1024) units /= 2;
+  const int64_t wgs = rows * ((tiles + units - 1) / units), rounds = (wgs + 511) / 512;
+  if (wgs < 512) return 0;
+  const double idle = (double)(rounds * 512 * units) / (double)(rows * tiles);
+  const double most = K == 64 ? (units == 2 ? 1.05 : 1.44) : (rounds < 3 ? 1.4 : 1.46);
+  return idle <= most ? units : 0;
+}
+
 gift_status launch_update(gift_ctx *ctx, const TileJob &j) {
   UArgs a{};
   for (int s = 0; s < j.nseg; ++s) {
@@ -1028,18 +1054,13 @@ gift_status launch_update(gift_ctx *ctx, const TileJob &j) {
   ProfileScope prof(ctx, j.kernel_family);
   dim3 grid((unsigned)((j.N + kColsPerUnit - 1) / kColsPerUnit), (unsigned)((j.M + 63) / 64),
             (unsigned)j.batch);
-  // large stores (the inverse transform): 128-row workgroups once they fill
-  // the chip's 512 slots (two per CU), over four or eight tiles while the grid
-  // then holds two rounds (8 x 4608 x 1536, rank 128, at 2 / 4 / 8 tiles: 273 /
-  // 237 / 232 us; 12 x 1024 x 2816, rank 64: 142 / 125 / 127)
+  // large stores (the inverse transform): 128-row workgroups, over four or
+  // eight tiles while the grid then holds two rounds (store_units)
   if (!j.amax && j.nseg == 1 && j.N % 4 == 0 && !j.d_tab && !j.seg[0].a.tab && !j.seg[0].b.tab &&
       (j.seg[0].K == 64 || j.seg[0].K == 128)) {
-    const int64_t rows = (j.M + 127) / 128 * j.batch, tiles = (j.N + 63) / 64;
-    int units = 8;
-    while (units > 2 && rows * ((tiles + units - 1) / units) < 1024) units /= 2;
-    const int64_t cols = (tiles + units - 1) / units;
-    if (rows * cols >= 512) {
-      const dim3 sgrid((unsigned)cols, (unsigned)((j.M + 127) / 128), (unsigned)j.batch);
+    const int units = store_units(j.M, j.N, j.batch, (int)j.seg[0].K);
+    if (units > 0) {
+      const dim3 sgrid((unsigned)((j.N + 64 * units - 1) / (64 * units)), (unsigned)((j.M + 127) / 128), (unsigned)j.batch);
       if (j.seg[0].K == 64)
         hipLaunchKernelGGL(update_store_kernel<4>, sgrid, dim3(kThreads), 0, ctx->stream, a, units);
       else

@@ -1,8 +1,8 @@
 """The inverse transform's launches of large grids, and tensors at any float's
 address (runs on an MI355X): the store kernel of 128-row workgroups over two,
 four and eight 64-column tiles (rows past the last workgroup, a last column
-unit of fewer tiles and one of a few columns), the staged projection with two
-strips per wave, and the unaligned store and projections in partials.
+unit of fewer tiles and one of a few columns) and the grids beside its rule,
+and the unaligned store and projections in partials.
 
 The reference is the inverse in float64 on the device.  Bar: 1e-6 of its norm.
 The float32 products keep W itself exactly, and the correction's two sums of at
@@ -57,27 +57,30 @@ def close(out, W, parts):
     assert ((out.double() - want).norm() / want.norm()).item() <= 1e-6
 
 
-def units_of(count, m, n):
-    """Tiles per workgroup of the store kernel (launch_update of
-    csrc/k_update.hip), 0 where the launch stays on update_kernel."""
+def units_of(count, m, n, r):
+    """store_units of csrc/k_update.hip: tiles per workgroup of the store
+    kernel, 0 where the launch stays on update_kernel."""
     rows, tiles = -(-m // 128) * count, -(-n // 64)
     units = 8
     while units > 2 and rows * -(-tiles // units) < 1024:
         units //= 2
-    return units if rows * -(-tiles // units) >= 512 else 0
+    wgs = rows * -(-tiles // units)
+    rounds = -(-wgs // 512)
+    idle = rounds * 512 * units / (rows * tiles)
+    most = (1.05 if units == 2 else 1.44) if r == 64 else (1.4 if rounds < 3 else 1.46)
+    return units if wgs >= 512 and idle <= most else 0
 
 
 @pytest.mark.parametrize("count,m,n,r,units", [
-    (5, 1061, 1500, 64, 2), (5, 1061, 1500, 128, 2),      # 24 tiles, the last of 28 columns
-    (2, 5465, 2820, 64, 4), (1, 11000, 2820, 128, 4),     # 45 tiles: a last unit of one
-    (3, 8100, 2820, 64, 8),
-    (9, 8100, 516, 128, 8),                               # nine tiles; two strips per projection wave
-    (8, 8177, 260, 64, 4),                                # (one part: 512 workgroups of 128 rows)
-    (4, 1061, 1500, 64, 0),                               # just too small
+    (8, 1061, 1500, 128, 2), (9, 2037, 836, 64, 2),       # 24 and 14 tiles, the last of 28 and 4 columns
+    (3, 5465, 2820, 64, 4), (5, 6100, 1540, 128, 4),      # 45 and 25 tiles: a last unit of one
+    (3, 8100, 2820, 64, 8), (8, 8100, 1028, 128, 8),      # last units of five tiles and of one
+    (8, 8177, 260, 128, 0), (8, 1061, 1500, 64, 0),       # much of the last round empty
+    (4, 1061, 1500, 64, 0),                               # too small
 ])
 def test_store_units(ctx, count, m, n, r, units):
     print(f"[case] inverse count={count} m={m} n={n} r={r} units={units}", flush=True)
-    assert units_of(count, m, n) == units
+    assert units_of(count, m, n, r) == units
     gen = torch.Generator().manual_seed(m + n + r)
     made = [factor(ctx, gen, m, n, r, IN) for _ in range(count)]
     means = [torch.randn((m, n), generator=gen).to(DEV) for _ in range(count)]
