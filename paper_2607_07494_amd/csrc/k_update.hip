@@ -684,8 +684,8 @@ __global__ __launch_bounds__(kThreads) void proj_kernel(const PArgs p) {
 // RAG: K or a row stride no multiple of 4, or an operand at no 16-byte address:
 // 16-byte loads at any float, a group that crosses the end of the row from its
 // last four floats, shifted and filled with zeros.
-// RG 16-row strips per wave: two when the grid still fills the chip, so that
-// each staged chunk of Y and each LDS fragment serves twice the rows.  blocks:
+// RG 16-row strips per wave: two for Q A when the grid still fills the chip, so
+// that each staged chunk of Y and each LDS fragment serves twice the rows.  blocks:
 // blocks of 16 NT columns, for the refresh's Q A at k > 128 (k = 256, six
 // factors of 4096: 1047 us on proj_kernel, whose waves read Q from L2 for 16
 // rows each, 617 here).
@@ -1194,8 +1194,12 @@ gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
     const int blocks = fold ? ct / fold : staged_t ? (a.C + 127) / 128 : 1;
     const int nt = ct / blocks;
     const bool rag = !staged_aligned(j);
-    // 128-row workgroups once they fill the chip's slots (two per CU)
-    const bool two = !rag && fold <= 4 && (a.M + 127) / 128 * parts * blocks * j.batch >= 512;
+    // Q A in 128-row workgroups once they fill the chip's slots (two per CU).
+    // (The decode's projections, shorter and in partials, stay at 64 rows:
+    // over 24 grids at ranks 16 to 128 128 rows took 0.88 to 1.17 of the time,
+    // 1.03 in the mean; 2 x 5465 x 2820 at rank 128 102 against 121 us, 8 x 4608 x
+    // 1536 173 against 171, 24 x 512 x 4096 at rank 64 88 against 82.)
+    const bool two = staged_t && fold <= 4 && (a.M + 127) / 128 * parts * blocks * j.batch >= 512;
     const int rows = two ? 128 : 64;
     const dim3 sgrid((unsigned)((a.M + rows - 1) / rows), (unsigned)(parts * blocks), (unsigned)j.batch);
 #define GIFT_STAGED(NT, RAG, RG, FOLD) \
@@ -1209,11 +1213,25 @@ gift_status launch_proj(gift_ctx *ctx, const TileJob &j) {
       else GIFT_STAGED(7, false, 1, true);
       return check_launch("proj_staged_kernel");
     }
-#define GIFT_PROJS(NT)                             \
-  do {                                             \
-    if (rag) GIFT_STAGED(NT, true, 1, false);      \
-    else if (two) GIFT_STAGED(NT, false, 2, false); \
-    else GIFT_STAGED(NT, false, 1, false);         \
+    if (staged_t) {   // wide blocks: 5 to 8 tiles
+      switch (nt) {
+#define GIFT_PROJT(NT)                            \
+  do {                                            \
+    if (two) GIFT_STAGED(NT, false, 2, false);    \
+    else GIFT_STAGED(NT, false, 1, false);        \
+  } while (0)
+        case 5: GIFT_PROJT(5); break;
+        case 6: GIFT_PROJT(6); break;
+        case 7: GIFT_PROJT(7); break;
+        default: GIFT_PROJT(8); break;
+#undef GIFT_PROJT
+      }
+      return check_launch("proj_staged_kernel");
+    }
+#define GIFT_PROJS(NT)                          \
+  do {                                          \
+    if (rag) GIFT_STAGED(NT, true, 1, false);   \
+    else GIFT_STAGED(NT, false, 1, false);      \
   } while (0)
     switch (nt) {
       case 1: GIFT_PROJS(1); break;
