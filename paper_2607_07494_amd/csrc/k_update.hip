@@ -1003,6 +1003,8 @@ bool update_kernel_eligible(const TileJob &j) {
 //   idle 1.19: 24 x 1061 x 1500 124 / 128 and 186 / 219 (four tiles)
 //   idle 1.42: 2 x 2048 x 2820 58.3 / 47.9 and 97.9 / 89.2 (two tiles, two rounds); 3 x 2048 x 2820 76.4 /
 //              69.3 and 128 / 139 (three rounds); 6 x 2048 x 2820 126 / 131 and 197 / 254 (four tiles)
+//   idle 1.59: 2 x 5465 x 2820 115 / 120 and 187 / 224, 1 x 11000 x 2820 at rank 128 150 / 164 (four tiles, three
+//              rounds); 6 x 1061 x 1500 41.9 / 32.9 and 59.9 / 57.7 (two tiles)
 //   idle 1.94: 3 x 1024 x 2816 49.3 / 40.7 and 81.9 / 75.3
 // (at rank 64 update_kernel holds twice the workgroups per CU and two tiles
 // save it less)
@@ -1013,7 +1015,7 @@ int store_units(int64_t M, int64_t N, int32_t batch, int K) {
   const int64_t wgs = rows * ((tiles + units - 1) / units), rounds = (wgs + 511) / 512;
   if (wgs < 512) return 0;
   const double idle = (double)(rounds * 512 * units) / (double)(rows * tiles);
-  const double most = K == 64 ? (units == 2 ? 1.05 : 1.44) : (rounds < 3 ? 1.4 : 1.46);
+  const double most = K == 64 ? (units == 2 ? 1.05 : 1.44) : (rounds < 3 ? 1.4 : (units == 2 ? 1.46 : 1.6));
   return idle <= most ? units : 0;
 }
 

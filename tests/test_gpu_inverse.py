@@ -67,13 +67,17 @@ def units_of(count, m, n, r):
     wgs = rows * -(-tiles // units)
     rounds = -(-wgs // 512)
     idle = rounds * 512 * units / (rows * tiles)
-    most = (1.05 if units == 2 else 1.44) if r == 64 else (1.4 if rounds < 3 else 1.46)
+    if r == 64:
+        most = 1.05 if units == 2 else 1.44
+    else:
+        most = 1.4 if rounds < 3 else 1.46 if units == 2 else 1.6
     return units if wgs >= 512 and idle <= most else 0
 
 
 @pytest.mark.parametrize("count,m,n,r,units", [
     (8, 1061, 1500, 128, 2), (9, 2037, 836, 64, 2),       # 24 and 14 tiles, the last of 28 and 4 columns
-    (3, 5465, 2820, 64, 4), (5, 6100, 1540, 128, 4),      # 45 and 25 tiles: a last unit of one
+    (3, 5465, 2820, 64, 4), (2, 5465, 2820, 128, 4),      # 45 and 25 tiles: a last unit of one
+    (5, 6100, 1540, 128, 4),
     (3, 8100, 2820, 64, 8), (8, 8100, 1028, 128, 8),      # last units of five tiles and of one
     (8, 8177, 260, 128, 0), (8, 1061, 1500, 64, 0),       # much of the last round empty
     (4, 1061, 1500, 64, 0),                               # too small
