@@ -978,6 +978,10 @@ bool update_kernel_eligible(const TileJob &j) {
   // (16 x 2900 x 2001, both sides at rank 64, 100-column blocks: 10.8 ms here,
   // 2.05 there).  (The rule sees what both passes share.)
   if (j.amax != nullptr && (j.N % 4 != 0 || K == 48 || K == 96 || !al16(j.D) || (j.ef && !al16(j.ef)))) {
+    // (both sides at ranks 96 and 128, 192 and 256 steps per tile, at one
+    // workgroup per CU: maxima of 6 x 700 x 515 45 and 52 us here, 29 and 35 there; of
+    // 6 x 700 x 2731 124 and 153 against 102 and 124)
+    if (j.nseg == 2 && K > 64) return false;
     const int64_t br = j.geom.br > 0 ? j.geom.br : j.M, bc = j.geom.bc > 0 ? j.geom.bc : j.N;
     if (!((br % 16 == 0 || br >= j.M) && (bc % 64 == 0 || bc >= j.N))) return false;
   }
