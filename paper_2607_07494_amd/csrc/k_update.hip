@@ -969,9 +969,15 @@ bool update_kernel_eligible(const TileJob &j) {
     if (g.a.ld % 4 || g.b.ld % 4 || g.a.bs % 4 || g.b.bs % 4) return false;
     if (!al16(g.a.ptr) || !al16(g.b.ptr)) return false;
   }
-  // (two-sided stores at rank 96, 192 steps per tile: 1400 x 4000 75 us here,
-  // 62 on the tile kernel)
-  if (j.amax == nullptr && j.nseg == 2 && K == 96 && j.N % 4 == 0) return false;
+  // Two-sided stores at rank 96, and at rank 128 of odd rows or addresses, stay
+  // on the tile kernel: 192 and 256 steps per tile at one workgroup per CU cost
+  // more than its smaller tiles (whole decodes at rank 96, here / there: 300 x
+  // 333 70 / 62 us, 1401 x 4001 165 / 149, 700 x 2731 92 / 86, 256 x 256 63 / 55, 1536 x 1536
+  // 109 / 92, 4096 x 4096 350 / 267; at rank 128: 130 x 129 74 / 66, 3001 x 1001 137 / 119,
+  // 700 x 2731 99 / 97).
+  if (j.amax == nullptr && j.nseg == 2 &&
+      (K == 96 || (K == 128 && (j.N % 4 != 0 || (j.D && !al16(j.D)) || (j.C && !al16(j.C))))))
+    return false;
   // Odd rows, odd addresses and ranks 48 and 96 come here for their maxima and
   // codes where a wave's 16 x 64 tile lies in one scale block; over other
   // blocks the per-element maxima cost more than the tile kernel's products
