@@ -83,3 +83,21 @@ def test_ragged_codec(ctx, N, m, n, r, sides, br, bc, ef, shared, shift):  # noq
     if r:
         assert rel(gpu_decode(ctx, f, mean), codec.decode(mean, fA, fG)) <= 1e-6
         f.close()
+
+
+@pytest.mark.parametrize("N,m,n,br,bc", [
+    (1, 40, 259, 0, 0), (1, 17, 771, 5, 100), (2, 33, 1027, 0, 128), (2, 16, 254, 0, 7), (3, 31, 131, 0, 64),
+    (3, 1500, 1503, 0, 128), (3, 1489, 1538, 7, 9), (4, 18, 67, 0, 0), (5, 18, 65, 0, 0),
+])
+def test_ragged_rank_sum(ctx, N, m, n, br, bc):  # noqa: F811
+    """Few ranks take wide workgroups (256 columns), three of them from 512
+    workgroups on: the mean bit for bit the oracle's."""
+    say(f"ragged rank sum N={N} m={m} n={n} block=({br},{bc})")
+    rng = np.random.default_rng(m + n)
+    codes = rng.integers(0, 256, (N, m, n)).astype(np.uint8)
+    codes[(codes & 0x7f) == 0x7f] = 0x38   # (no NaN)
+    nbr, nbc = gift.scale_grid(m, n, br, bc)
+    scales = rng.uniform(1e-6, 1e-3, (N, nbr, nbc)).astype(np.float32)
+    mean = torch.full((m, n), float("nan"), device=DEV)
+    gift.reduce_local(ctx, t(codes), t(scales), mean, br, bc)
+    np.testing.assert_array_equal(mean.cpu().numpy(), codec.reduce_local(codes, scales, br, bc))
