@@ -22,11 +22,12 @@
 // the block's sub-slots when the block row changes.
 //
 // Measured against the sweep kernel, maxima / codes: 8192 x 1536, 16 ranks,
-// rank 128: 258 / 304 -> 221 / 271 us (W at 3.6 TB/s; with P half missing its
-// L2 the pass moves 1.05 GB at 4.7 TB/s); 1536 x 4096 with the residual: 188 /
-// 272 -> 165 / 264; 5632 x 1024, 8 ranks, rank 64: 42 / 53 -> 35 / 45.  Not
-// faster: two tiles' products at a time, W two tiles ahead, 32x32x16 products
-// (the matrix cores do not bound the pass), non-temporal loads of W.
+// rank 128: 258 / 304 -> 221 / 271 us; 5632 x 1024, 8 ranks, rank 64: 42 / 53 -> 35 /
+// 45.  With the residual the gain depends on the launch (lr_strip_eligible):
+// 3072 x 4096, 8 ranks, rank 128: 175 / 261 -> 160 / 261; 2048 columns at a third
+// of that size: 66 / 99 -> 54 / 87.  Not faster: two tiles' products at a time, W
+// two tiles ahead, 32x32x16 products (the matrix cores do not bound the pass),
+// non-temporal loads of W.
 
 #include <algorithm>
 #include <type_traits>
@@ -345,8 +346,29 @@ bool lr_strip_eligible(const TileJob &j) {
   if ((int64_t)j.batch * j.geom.nbr * j.geom.nbc * kAmaxSlots >= (1LL << 31)) return false;
   const int64_t groups = (j.M + 31) / 32 * j.batch;
   if (groups >= (1LL << 30)) return false;
+  const int pairs = (int)(j.N / 128);
   int cp = 0;
-  return pick_strips((int)(j.N / 128), groups, (int)K, j.ef != nullptr, &cp) > 0;
+  const int strips = pick_strips(pairs, groups, (int)K, j.ef != nullptr, &cp);
+  if (strips == 0) return false;
+  // With the residual, twice the bytes in flight, an idle quarter of the chip
+  // costs more than the image's copies did, and past the last-level cache the
+  // code pass moves its bytes no faster than the sweep: at 8 ranks, maxima and
+  // codes, sweep -> strips,
+  //   2816 columns (0.69 of the chip): 80 MB at rank 128 45 -> 50 and 64 -> 69 us, 320 MB 163 -> 168 and
+  //     242 -> 284; 1536 columns (0.75), 48 MB 28 -> 30 and 40 -> 43
+  //   1024 columns (all of it): 200 MB at rank 64 / 128 108 / 120 -> 93 / 104 and 152 / 162 -> 139 / 141, 320 MB
+  //     135 / 158 -> 126 / 137 and 205 / 225 -> 210 / 221
+  //   1664 columns (0.81): 160 MB at rank 128 91 -> 81 and 138 -> 131, 384 MB 193 -> 184 and 290 -> 307
+  // (Without it strips are at worst even: 2816 columns, 160 MB 57.2 -> 56.9 and
+  // 70.5 -> 68.9.)  The code pass at rank 64 has a sweep only where the columns
+  // are whole 256-column ranges; the per-unit kernel is slower than strips
+  // throughout (1664 columns, 160 MB: 144 -> 122).
+  if (j.ef && !(j.codes && K == 64 && j.N % 256 != 0)) {
+    const double fill = (double)pairs * (kXcds * (kCusPerXcd / strips)) / (double)(kXcds * kCusPerXcd * cp);
+    if (fill < 0.8) return false;
+    if (j.codes && 4 * j.M * j.N * j.batch > (224LL << 20) && (K < 128 || fill < 0.85)) return false;
+  }
+  return true;
 }
 
 gift_status launch_lr_strip(gift_ctx *ctx, const TileJob &j) {
