@@ -1487,7 +1487,7 @@ bool lr_quant_reads_raw(const TileJob &j) {
 bool lr_update_eligible(const TileJob &j) {
   const bool mx = j.mx_codes != nullptr;
   if (!j.split3 || (j.amax == nullptr && !mx) || j.nseg < 1 || j.nseg > 2 || j.N % 4 != 0) return false;
-  if (mx && (j.N % 32 != 0 || j.codes != nullptr || (reinterpret_cast<uintptr_t>(j.mx_codes) & 1))) return false;
+  if (mx && (j.N % 32 != 0 || j.codes != nullptr || (reinterpret_cast<uintptr_t>(j.mx_codes) & 3))) return false;
   if (j.M * j.N >= (1LL << 29)) return false;   // one rank's slice within a 32-bit buffer range
   const int64_t K = j.seg[0].K;
   if (K <= 0 || K > 128 || K % 4 != 0) return false;
