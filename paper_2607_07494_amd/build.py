@@ -71,35 +71,42 @@ def _compile(src: str) -> str:
 
 def two_wave_scratch():
     """{kernel: scratch bytes per lane} of the two-waves-per-SIMD update
-    variants (lr_update_kernel_o2, lr_sweep_kernel), from the compiler's
-    resource report."""
+    variants (lr_update_kernel_o2, lr_sweep_kernel, lr_strip_kernel), from the
+    compiler's resource reports."""
     import re
-    path = os.path.join(BUILD, "k_lowrank.hip.o.resources.txt")
     out, name = {}, None
-    for line in open(path):
-        m = re.search(r"Function Name: (\S+)", line)
-        if m:
-            name = m.group(1)
-            continue
-        m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
-        if m and name and ("lr_update_kernel_o2" in name or "lr_sweep_kernel" in name):
-            out[name] = int(m.group(1))
+    for src in sorted(RESOURCE_REPORT):
+        for line in open(os.path.join(BUILD, src + ".o.resources.txt")):
+            m = re.search(r"Function Name: (\S+)", line)
+            if m:
+                name = m.group(1)
+                continue
+            m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
+            if m and name and any(k in name for k in ("lr_update_kernel_o2", "lr_sweep_kernel", "lr_strip_kernel")):
+                out[name] = int(m.group(1))
     return out
+
+
+# Scratch that was there when the variant was measured: the strips' maxima at
+# rank 128, two tile pairs, with the residual.
+KNOWN_SCRATCH = {"lr_strip_kernelILi1ELi4ELi2ELb1EE": 8}
 
 
 def check_two_wave_spills(verbose: bool = False):
     """The two-wave update variants exist to hold two waves per SIMD with no
-    scratch; a toolchain or code change that makes one spill would slow the
-    rank-128 encode without changing its results, so the build fails."""
+    scratch; a toolchain or code change that makes one spill (or spill more)
+    would slow the rank-128 encode without changing its results, so the build
+    fails."""
     scratch = two_wave_scratch()
-    if not scratch:
+    if not any("lr_sweep_kernel" in k for k in scratch) or not any("lr_strip_kernel" in k for k in scratch):
         raise RuntimeError("no resource report for the two-wave update kernels")
-    bad = {k: v for k, v in scratch.items() if v > 0}
+    bad = {k: v for k, v in scratch.items()
+           if v > max((most for known, most in KNOWN_SCRATCH.items() if known in k), default=0)}
     if bad:
         raise RuntimeError("two-wave update kernels spill to scratch: " +
                            ", ".join(f"{k} ({v} B/lane)" for k, v in sorted(bad.items())))
     if verbose:
-        print(f"{len(scratch)} two-wave update kernels, no scratch")
+        print(f"{len(scratch)} two-wave update kernels, no scratch beyond the known {sum(v > 0 for v in scratch.values())}")
 
 
 def _link(objs, out):
