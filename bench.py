@@ -47,17 +47,18 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# Source file of each kernel family: a measured HBM traffic figure (profiles/,
-# rocprofv3 FETCH_SIZE / WRITE_SIZE) is reported only while this file is
-# unchanged since the counters were taken.
+# Source file(s) of each kernel family: a measured HBM traffic figure
+# (profiles/, rocprofv3 FETCH_SIZE / WRITE_SIZE) is reported only while they
+# are unchanged since the counters were taken.
+STRIP_AND_SWEEP = ("paper_2607_07494_amd/csrc/k_strip.hip", "paper_2607_07494_amd/csrc/k_lowrank.hip")
 FAMILY_SOURCE = {
     "syrk": "paper_2607_07494_amd/csrc/k_syrk.hip",
     "amax": "paper_2607_07494_amd/csrc/k_stream.hip",
     "quant": "paper_2607_07494_amd/csrc/k_stream.hip",
     "reduce": "paper_2607_07494_amd/csrc/k_stream.hip",
     "project": "paper_2607_07494_amd/csrc/k_lowrank.hip",
-    "update_amax": "paper_2607_07494_amd/csrc/k_lowrank.hip",
-    "update_quant": "paper_2607_07494_amd/csrc/k_lowrank.hip",
+    "update_amax": STRIP_AND_SWEEP,
+    "update_quant": STRIP_AND_SWEEP,
     "update_store": "paper_2607_07494_amd/csrc/k_update.hip",
     "decode_project": "paper_2607_07494_amd/csrc/k_update.hip",
     "chol_transform": "paper_2607_07494_amd/csrc/k_chol.hip",
@@ -156,9 +157,13 @@ def parse():
 
 
 def source_sha256(rel):
+    """SHA-256 of one source file, or of several one after another."""
     import hashlib
-    with open(os.path.join(ROOT, rel), "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()
+    h = hashlib.sha256()
+    for name in (rel,) if isinstance(rel, str) else rel:
+        with open(os.path.join(ROOT, name), "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()
 
 
 def measured_traffic(family, workload):

@@ -81,3 +81,25 @@ def test_steps_begin_on_every_stream(durations):
             st.run(durations[(i + step) % len(durations)])
         bench.join(main, streams, Event)
         assert main.now - begin == max(durations)
+
+
+def test_traffic_goes_with_its_sources(tmp_path, monkeypatch):
+    """A counted HBM figure is reported while every source of its family is the
+    one it was counted on, and no longer."""
+    for name in ("a.hip", "b.hip"):
+        (tmp_path / name).write_text(name)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    monkeypatch.setattr(bench, "FAMILY_SOURCE", {"update_amax": ("a.hip", "b.hip")})
+    monkeypatch.setattr(bench, "TRAFFIC_GLOB", str(tmp_path / "*.md"))
+    line = "traffic: family=update_amax workload=w bytes_per_launch=12 sha256=%s\n"
+    (tmp_path / "t.md").write_text(line % bench.source_sha256(("a.hip", "b.hip")))
+    assert bench.measured_traffic("update_amax", "w") == 12
+    assert bench.measured_traffic("update_amax", "v") is None
+    (tmp_path / "a.hip").write_text("c")
+    assert bench.measured_traffic("update_amax", "w") is None
+
+
+def test_families_name_files_that_are_there():
+    for rel in bench.FAMILY_SOURCE.values():
+        assert len(bench.source_sha256(rel)) == 64
+    assert "paper_2607_07494_amd/csrc/k_strip.hip" in bench.FAMILY_SOURCE["update_quant"]
