@@ -1137,7 +1137,12 @@ bool proj_kernel_eligible(const TileJob &j) {
 }
 
 // The short-chain projection: a plain k-major product whose tile grid would
-// leave most of the chip idle.
+// leave most of the chip idle.  The whole encode with it (and the update above)
+// against the tile kernel, six ranks, at ranks 8 / 48 / 128, us: 700 x 131 31 / 38 / 46
+// -> 25 / 27 / 41, 700 x 2731 189 / 253 / 305 -> 124 / 103 / 217, 3001 x 1001 185 / 259 / 366
+// -> 137 / 142 / 297, 96 x 4001 (rank 8, 48) 160 / 234 -> 82 / 91; of 93 grids of 96 to
+// 3001 rows, 131 to 4001 columns and ranks 8 to 128 one is even (3001 x 131 at rank
+// 128, 93) and all others faster.
 bool proj_chain_eligible(const TileJob &j) {
   const Segment &g = j.seg[0];
   return j.nseg == 1 && j.amax == nullptr && g.a.kmajor && g.b.kmajor && !job_has_tabs(j) && !j.decode_tab &&
