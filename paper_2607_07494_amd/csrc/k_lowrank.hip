@@ -1331,9 +1331,8 @@ int lr_proj_parts(int64_t M, int64_t K, int32_t batch) {
   // projection 7 % faster and the concurrent step 1.5 %). Launches of 128
   // row tiles or more stop at two partials (one workgroup per CU already):
   // on the Llama-600M o and down buckets (192 tiles of 16 ranks) 2 instead
-  // of 4 made the projection about 2 % slower alone and the four-stream
-  // codec step 37.38-37.50 -> 37.29-37.33 ms over three alternating runs
-  // (half the partials' traffic; the step is bound by its HBM bytes)
+  // of 4 made the projection about 2 % slower alone at half the partials'
+  // traffic, which the step's other streams compete for
   const int64_t tiles = (M + kProjRows - 1) / kProjRows * batch;
   const int max_parts = tiles >= 128 ? 2 : 4;
   int parts = 1;
@@ -1571,11 +1570,9 @@ gift_status launch_lr_update(gift_ctx *ctx, const TileJob &j) {
                      (int64_t)j.batch * j.geom.nbr * j.geom.nbc * kAmaxSlots < (1LL << 31);
   if (sweep) {
     // runs of four units (eight 64-column tiles) once the launch fills four
-    // rounds of resident workgroups (two per CU), shorter runs below.
-    // Measured on the Llama-600M buckets in the four-stream step: runs of
-    // 3-4 units 38.8-39.6 ms per codec step, 5-6 units 43-45 ms, runs sized
-    // for one or two rounds 46-47 ms (the same kernels in isolation differ
-    // by under 5 %)
+    // rounds of resident workgroups (two per CU), shorter runs below (runs of
+    // 3 to 6 units and of one or two rounds are within 5 % of each other on
+    // the Llama-600M buckets alone)
     const int64_t upw = sw_units >= 4 * 512 ? 4 : std::max<int64_t>(1, sw_units / 512);
     a.upw = (int)upw;
     a.col_img = j.col_img;

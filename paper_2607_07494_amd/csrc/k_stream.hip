@@ -473,8 +473,7 @@ gift_status launch_stream_reduce(gift_ctx *ctx, const uint8_t *codes, const floa
   // 1536-column matrix would leave a quarter of its lanes idle. Measured on
   // the Llama-600M set (16 ranks): rank sums 3.12 -> 2.72 ms per step in
   // isolation (4.35 -> 5.0 TB/s by (N + 4) bytes per element); one row per
-  // group instead of two (more waves per SIMD) 2.61 ms alone but 5-6 ms
-  // slower four-stream steps
+  // group instead of two (more waves per SIMD) 2.61 ms
   const auto idle = [&](int64_t cpl) { return (n + 64 * cpl - 1) / (64 * cpl) * 64 * cpl - n; };
   const bool mid = n % 8 == 0 && g.bc % 8 == 0 && aligned && idle(8) < idle(16);
   const bool wide = !mid && n % 16 == 0 && g.bc % 16 == 0 && aligned;

@@ -83,6 +83,25 @@ def test_steps_begin_on_every_stream(durations):
         assert main.now - begin == max(durations)
 
 
+@pytest.mark.parametrize("used", [[1, 2], [0], [2, 2, 0], []])
+def test_steps_wait_for_streams_with_work(used):
+    """Streams that get no work are neither waited for nor held: a step ends
+    with the streams that have some."""
+    streams = [Stream() for _ in range(4)]
+    main = streams[0]
+    busy = bench.with_work(streams, used)
+    assert busy == [streams[i] for i in sorted(set(used))]
+    for step in range(3):
+        bench.join(main, busy, Event)
+        begin = main.now
+        bench.start_together(main, busy, Event)
+        for i in set(used):
+            streams[i].run(1.0 + i)
+        bench.join(main, busy, Event)
+        assert main.now - begin == max([1.0 + i for i in used], default=0.0)
+    assert all(streams[i].now == 0.0 for i in range(1, 4) if i not in used)
+
+
 def test_traffic_goes_with_its_sources(tmp_path, monkeypatch):
     """A counted HBM figure is reported while every source of its family is the
     one it was counted on, and no longer."""
